@@ -428,7 +428,7 @@ size_t dwkv_sketch_workspace_bytes(const dwkv_dims* dims, int64_t n_tokens);
  *          encoding, Z = 1 values)
  *   omega: fp16 [w * n_tokens][r_b], row l * n_tokens + t: the random sketch
  *          matrix (transposed), drawn by the caller and shared by heads and Z
- * WRITES cache->basis[seq][window] (all heads, both Z); nothing else.  Two
+ * WRITES cache->basis[seq][window] (all heads, both Z); nothing else.  Three
  * launches.  All pointers 16-byte aligned. */
 dwkv_status dwkv_sketch_basis(const dwkv_dims* dims, const dwkv_cache* cache, int32_t window, int32_t seq,
                               const void* x, const void* omega, int64_t n_tokens, void* workspace,

@@ -394,12 +394,13 @@ struct SketchArgs {
   const uint16_t* x;           // fp16 [w][2][n_tokens][Hkv][d] prefill keys (Z = 0) and values (Z = 1)
   const uint16_t* omega;       // fp16 [w * n_tokens][rb] sketch matrix, row l * n_tokens + t
   double* part;                // [n_chunks][Hkv][2][rb][d] sketch partials
-  double* q;                   // [Hkv][2][rb][d] orthonormal rows
+  double* q;                   // [Hkv][2][rb][d] the sketch rows Y (chunk partials summed)
   uint16_t* basis;             // the (sequence, window)'s basis [Hkv][2][rb][d], written
   int64_t n_tokens;
-  int32_t w, n_kv_heads, rb, n_chunks;
+  int32_t w, n_kv_heads, rb;
+  int32_t chunk_rows, layer_chunks, n_chunks;   // a chunk is chunk_rows tokens of one layer
 };
-int sketch_chunks(int64_t rows);
+int sketch_chunk_rows(int64_t n_tokens, int w, int n_kv_heads);
 hipError_t launch_sketch(const SketchArgs& a, hipStream_t s);
 hipError_t launch_residual_map(const uint32_t* off, const uint8_t* idx, const uint8_t* val,
                                const uint16_t* scale, int64_t t0, int64_t t1, int64_t slab_len,

@@ -4,11 +4,22 @@
 // and Omega (r_b x (w T_b)) a caller-drawn random matrix; the basis is the
 // Gram-Schmidt orthonormalization of Y's rows, rounded to fp16.
 //
-// Two launches: (1) split-K sketch partials, one workgroup per (4096-row
-// chunk, head, Z), thread c owning channel c and accumulating r_b products in
-// float64 (fp16 products are exact there); (2) per (head, Z), one wave sums
-// the chunk partials in order and orthonormalizes the rows in float64,
-// lanes owning channel pairs and wave shuffles forming the dot products.
+// Three launches:
+//  1. split-K sketch partials on v_mfma_f64_16x16x4_f64 (fp16 products are
+//     exact in float64), one workgroup per (row chunk of one layer, head, Z),
+//     each of its 4 waves owning 32 channels and every row of Omega.  Bound by
+//     the float64 matrix rate: the 51.5 GFLOP of a 4 x 64K window (r_b 48, 8
+//     heads) take 0.87 ms, 59 TFLOP/s of the published 78.6; one thread per
+//     channel on float64 FMAs, converting Omega's row in every thread, took
+//     6.1 ms.
+//  2. the chunk partials summed in chunk order, one thread per element (50 MB
+//     read once in 10 us; inside the orthonormalization one compute unit would
+//     pull each head's share).
+//  3. the orthonormalization, one 16-wave workgroup per (head, Z): modified
+//     Gram-Schmidt from the left, every later row updated as soon as a row is
+//     final, rows dealt to the waves in turn.  Bound by its serial chain
+//     (r_b steps of a normalization, a barrier and a dot product): 40 us at
+//     r_b 48, against 1.1 ms for one wave that also summed the partials.
 #include "entry.h"
 #include "internal.h"
 
@@ -16,84 +27,211 @@ namespace dwkv {
 namespace {
 
 constexpr int D = kHeadDim;
-constexpr int kSkRows = 4096;            // sketch rows (tokens x layers) per workgroup
+constexpr int kSkWaves = 4;                     // waves of a partial workgroup
+constexpr int kSkU = 8;                         // 4-row MFMA steps per load group
+constexpr int kSkGroup = 4 * kSkU;              // rows per load group
+constexpr int kOrthWaves = 16;
 
-template <int RB>
-__global__ __launch_bounds__(D) void sketch_partial_kernel(const SketchArgs a) {
-  const int chunk = blockIdx.x, h = blockIdx.y, z = blockIdx.z, c = threadIdx.x;
-  const int64_t N = (int64_t)a.w * a.n_tokens;
-  const int64_t r0 = (int64_t)chunk * kSkRows, r1 = min(r0 + (int64_t)kSkRows, N);
-  double acc[RB];
+typedef double d4 __attribute__((ext_vector_type(4)));
+
+// Loads of one group of kSkGroup rows: step u of lane (r, kk) is row 4 u + kk.
+template <int NS>
+struct SkRows {
+  uint32_t x[kSkU];                             // channels 2 r, 2 r + 1 of the wave's 32
+  uint32_t om[kSkU][NS % 2 ? NS : NS / 2];      // Omega entries NS r .. NS r + NS - 1
+};
+
+template <int NS, bool EDGE>
+__device__ __forceinline__ void sk_load(SkRows<NS>& f, const uint16_t* x, const uint16_t* om, int row0, int rows,
+                                        int64_t xstride, int kk) {
 #pragma unroll
-  for (int k = 0; k < RB; ++k) acc[k] = 0.0;
-  for (int64_t r = r0; r < r1; ++r) {
-    const int64_t l = r / a.n_tokens, t = r - l * a.n_tokens;
-    const double xv = (double)half_bits_to_float(a.x[(((l * 2 + z) * a.n_tokens + t) * a.n_kv_heads + h) * D + c]);
-    const uint16_t* om = a.omega + r * RB;             // the same row for every thread
+  for (int u = 0; u < kSkU; ++u) {
+    const int row = row0 + 4 * u + kk;
+    const int rc = EDGE ? min(row, rows - 1) : row;
+    const uint16_t* o = om + (int64_t)rc * (16 * NS);
+    f.x[u] = *reinterpret_cast<const uint32_t*>(x + rc * xstride);
+    if constexpr (NS % 2) {
 #pragma unroll
-    for (int k = 0; k < RB; ++k) acc[k] = __builtin_fma((double)half_bits_to_float(om[k]), xv, acc[k]);
+      for (int s = 0; s < NS; ++s) f.om[u][s] = o[s];
+    } else {
+#pragma unroll
+      for (int s = 0; s < NS / 2; ++s) f.om[u][s] = reinterpret_cast<const uint32_t*>(o)[s];
+    }
+    if (EDGE && row >= rows) {                  // rows past the chunk add nothing
+      f.x[u] = 0u;
+#pragma unroll
+      for (int s = 0; s < (NS % 2 ? NS : NS / 2); ++s) f.om[u][s] = 0u;
+    }
   }
-  double* out = a.part + (((int64_t)chunk * a.n_kv_heads + h) * 2 + z) * RB * D;
+}
+
+template <int NS>
+__device__ __forceinline__ void sk_mma(d4 (&acc)[NS][2], const SkRows<NS>& f) {
 #pragma unroll
-  for (int k = 0; k < RB; ++k) out[(int64_t)k * D + c] = acc[k];
+  for (int u = 0; u < kSkU; ++u) {
+    const double b0 = (double)half_bits_to_float((uint16_t)(f.x[u] & 0xffffu));
+    const double b1 = (double)half_bits_to_float((uint16_t)(f.x[u] >> 16));
+#pragma unroll
+    for (int s = 0; s < NS; ++s) {
+      const uint32_t w = NS % 2 ? f.om[u][s] : f.om[u][s / 2] >> (16 * (s & 1));
+      const double a = (double)half_bits_to_float((uint16_t)(w & 0xffffu));
+      acc[s][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, b0, acc[s][0], 0, 0, 0);
+      acc[s][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, b1, acc[s][1], 0, 0, 0);
+    }
+  }
+}
+
+// grid (w * chunks per layer, Hkv, 2).  Of the MFMA operands, lane (r, kk) =
+// (lane % 16, lane / 16) holds row r (A) or column r (B) at depth kk, and the
+// result's rows 4 i + kk of column r.  Operand rows and columns are dealt so
+// that a lane's loads are contiguous: A row r of tile s is Omega entry
+// NS r + s, B column r of tile c is channel 2 r + c of the wave's 32.
+template <int RB>
+__global__ __launch_bounds__(64 * kSkWaves) void sketch_partial_kernel(const SketchArgs a) {
+  constexpr int NS = RB / 16;
+  const int chunk = blockIdx.x, h = blockIdx.y, z = blockIdx.z;
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  const int r = lane & 15, kk = lane >> 4;
+  const int l = chunk / a.layer_chunks;
+  const int64_t t0 = (int64_t)(chunk % a.layer_chunks) * a.chunk_rows;
+  const int rows = (int)min((int64_t)a.chunk_rows, a.n_tokens - t0);
+  const int64_t xstride = (int64_t)a.n_kv_heads * D;
+  const uint16_t* x = a.x + (((int64_t)l * 2 + z) * a.n_tokens + t0) * xstride + (int64_t)h * D + 32 * wv + 2 * r;
+  const uint16_t* om = a.omega + ((int64_t)l * a.n_tokens + t0) * RB + NS * r;
+  d4 acc[NS][2];
+#pragma unroll
+  for (int s = 0; s < NS; ++s) acc[s][0] = acc[s][1] = d4{0.0, 0.0, 0.0, 0.0};
+  const int full = rows / kSkGroup;             // the next group's loads run under this one's products
+  SkRows<NS> cur, nxt;
+  if (full > 0) sk_load<NS, false>(cur, x, om, 0, rows, xstride, kk);
+  for (int g = 0; g + 1 < full; ++g) {
+    sk_load<NS, false>(nxt, x, om, (g + 1) * kSkGroup, rows, xstride, kk);
+    sk_mma<NS>(acc, cur);
+    cur = nxt;
+  }
+  if (full > 0) sk_mma<NS>(acc, cur);
+  if (rows % kSkGroup) {
+    sk_load<NS, true>(cur, x, om, full * kSkGroup, rows, xstride, kk);
+    sk_mma<NS>(acc, cur);
+  }
+  double* out = a.part + (((int64_t)chunk * a.n_kv_heads + h) * 2 + z) * RB * D + 32 * wv + 2 * r;
+#pragma unroll
+  for (int s = 0; s < NS; ++s)
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      *reinterpret_cast<double2*>(out + (int64_t)(NS * (4 * i + kk) + s) * D) = make_double2(acc[s][0][i], acc[s][1][i]);
+}
+
+// Y: the chunk partials summed in chunk order, one thread per element.
+__global__ __launch_bounds__(256) void sketch_sum_kernel(const SketchArgs a) {
+  const int64_t n = (int64_t)a.n_kv_heads * 2 * a.rb * D, e = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (e >= n) return;
+  double y = 0.0;
+#pragma unroll 8
+  for (int ch = 0; ch < a.n_chunks; ++ch) y += a.part[ch * n + e];
+  a.q[e] = y;
+}
+
+// Sum over the wave: DPP inside each row of 16 lanes, then the four rows'
+// sums read into scalar registers.  Every lane returns the same bits.
+template <int CTRL>
+__device__ __forceinline__ double dpp_d(double v) {
+  const uint64_t u = __builtin_bit_cast(uint64_t, v);
+  const uint32_t lo = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)u, CTRL, 0xF, 0xF, false);
+  const uint32_t hi = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)(u >> 32), CTRL, 0xF, 0xF, false);
+  return __builtin_bit_cast(double, (uint64_t)hi << 32 | lo);
+}
+
+__device__ __forceinline__ double lane_d(double v, int l) {
+  const uint64_t u = __builtin_bit_cast(uint64_t, v);
+  const uint32_t lo = __builtin_amdgcn_readlane((int)(uint32_t)u, l);
+  const uint32_t hi = __builtin_amdgcn_readlane((int)(uint32_t)(u >> 32), l);
+  return __builtin_bit_cast(double, (uint64_t)hi << 32 | lo);
 }
 
 __device__ __forceinline__ double wave_sum_d(double v) {
-#pragma unroll
-  for (int o = 32; o >= 1; o >>= 1) v += __shfl_xor(v, o);
-  return v;
+  v += dpp_d<0xB1>(v);                          // quad_perm(1,0,3,2)
+  v += dpp_d<0x4E>(v);                          // quad_perm(2,3,0,1)
+  v += dpp_d<0x141>(v);                         // row_half_mirror
+  v += dpp_d<0x140>(v);                         // row_mirror
+  return (lane_d(v, 0) + lane_d(v, 16)) + (lane_d(v, 32) + lane_d(v, 48));
 }
 
-// grid (Hkv, 2), one wave: lane l owns channels 2l, 2l + 1
+// grid (Hkv, 2): row i belongs to wave i % 16, lane l owns channels 2l, 2l+1.
+// Step i: the owner of row i (by now free of the rows before it) normalizes
+// and publishes it, then every wave takes its component out of its later rows
+// -- for each row the subtractions of modified Gram-Schmidt, in their order.
+// The published row alternates between two buffers, so one barrier per step
+// is enough: a wave that writes a buffer again has passed the barrier that
+// every reader of its old content reached afterwards.
 template <int RB>
-__global__ __launch_bounds__(64) void sketch_orth_kernel(const SketchArgs a) {
-  const int h = blockIdx.x, z = blockIdx.y, lane = threadIdx.x;
-  const int c0 = 2 * lane;
-  double* q = a.q + ((int64_t)h * 2 + z) * RB * D;      // orthonormal rows (float64)
-  // Y rows: the chunk partials summed in chunk order
+__global__ __launch_bounds__(64 * kOrthWaves) void sketch_orth_kernel(const SketchArgs a) {
+  constexpr int NR = RB / kOrthWaves;
+  __shared__ double2 qrow[2][D / 2];
+  __shared__ double nmax[kOrthWaves];
+  const int h = blockIdx.x, z = blockIdx.y, lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  const double2* y = reinterpret_cast<const double2*>(a.q + ((int64_t)h * 2 + z) * RB * D);
+  uint32_t* bout = reinterpret_cast<uint32_t*>(a.basis + ((int64_t)h * 2 + z) * RB * D);
+  double2 v[NR];
   double ymax = 0.0;
-  for (int k = 0; k < RB; ++k) {
-    double y0 = 0.0, y1 = 0.0;
-    for (int ch = 0; ch < a.n_chunks; ++ch) {
-      const double* p = a.part + (((int64_t)ch * a.n_kv_heads + h) * 2 + z) * RB * D + (int64_t)k * D + c0;
-      y0 += p[0];
-      y1 += p[1];
-    }
-    q[(int64_t)k * D + c0] = y0;
-    q[(int64_t)k * D + c0 + 1] = y1;
-    ymax = fmax(ymax, sqrt(wave_sum_d(y0 * y0 + y1 * y1)));
-  }
-  // the rows' own lanes rewrite them, so program order makes them visible
+#pragma unroll
+  for (int j = 0; j < NR; ++j) v[j] = y[(kOrthWaves * j + wv) * (D / 2) + lane];
+#pragma unroll
+  for (int j = 0; j < NR; ++j) ymax = fmax(ymax, sqrt(wave_sum_d(v[j].x * v[j].x + v[j].y * v[j].y)));
+  if (lane == 0) nmax[wv] = ymax;
+  __syncthreads();
+#pragma unroll
+  for (int w = 0; w < kOrthWaves; ++w) ymax = fmax(ymax, nmax[w]);
   const double floor_n = 1e-9 * ymax;
-  uint16_t* bout = a.basis + ((int64_t)h * 2 + z) * RB * D;
-  for (int i = 0; i < RB; ++i) {
-    double v0 = q[(int64_t)i * D + c0], v1 = q[(int64_t)i * D + c0 + 1];
-    for (int j = 0; j < i; ++j) {                       // modified Gram-Schmidt
-      const double q0 = q[(int64_t)j * D + c0], q1 = q[(int64_t)j * D + c0 + 1];
-      const double dot = wave_sum_d(v0 * q0 + v1 * q1);
-      v0 -= dot * q0;
-      v1 -= dot * q1;
+#pragma unroll
+  for (int j = 0; j < NR; ++j) {
+    for (int o = 0; o < kOrthWaves; ++o) {      // row 16 j + o
+      const int buf = o & 1;
+      if (wv == o) {
+        const double n = sqrt(wave_sum_d(v[j].x * v[j].x + v[j].y * v[j].y));
+        if (n > floor_n && n > 0.0) {
+          v[j].x /= n;
+          v[j].y /= n;
+        } else {
+          v[j] = make_double2(0.0, 0.0);
+        }
+        qrow[buf][lane] = v[j];
+        const uint32_t lo = __builtin_bit_cast(uint16_t, (_Float16)(float)v[j].x);
+        const uint32_t hi = __builtin_bit_cast(uint16_t, (_Float16)(float)v[j].y);
+        bout[(kOrthWaves * j + o) * (D / 2) + lane] = lo | hi << 16;
+      }
+      __syncthreads();
+      const double2 q = qrow[buf][lane];
+#pragma unroll
+      for (int k = j; k < NR; ++k) {
+        if (k == j && wv <= o) continue;        // rows up to this one are final
+        const double dot = wave_sum_d(v[k].x * q.x + v[k].y * q.y);
+        v[k].x -= dot * q.x;
+        v[k].y -= dot * q.y;
+      }
     }
-    const double n = sqrt(wave_sum_d(v0 * v0 + v1 * v1));
-    if (n > floor_n && n > 0.0) { v0 /= n; v1 /= n; } else { v0 = 0.0; v1 = 0.0; }
-    q[(int64_t)i * D + c0] = v0;
-    q[(int64_t)i * D + c0 + 1] = v1;
-    const uint32_t pk = (uint32_t)__builtin_bit_cast(uint16_t, (_Float16)(float)v0) |
-                        ((uint32_t)__builtin_bit_cast(uint16_t, (_Float16)(float)v1) << 16);
-    *reinterpret_cast<uint32_t*>(bout + (int64_t)i * D + c0) = pk;
   }
 }
 
 template <int RB>
 hipError_t launch_sketch_rb(const SketchArgs& a, hipStream_t s) {
-  hipLaunchKernelGGL(sketch_partial_kernel<RB>, dim3(a.n_chunks, a.n_kv_heads, 2), dim3(D), 0, s, a);
-  hipLaunchKernelGGL(sketch_orth_kernel<RB>, dim3(a.n_kv_heads, 2), dim3(64), 0, s, a);
+  const unsigned n = (unsigned)a.n_kv_heads * 2 * RB * D;
+  hipLaunchKernelGGL(sketch_partial_kernel<RB>, dim3(a.n_chunks, a.n_kv_heads, 2), dim3(64 * kSkWaves), 0, s, a);
+  hipLaunchKernelGGL(sketch_sum_kernel, dim3((n + 255) / 256), dim3(256), 0, s, a);
+  hipLaunchKernelGGL(sketch_orth_kernel<RB>, dim3(a.n_kv_heads, 2), dim3(64 * kOrthWaves), 0, s, a);
   return hipGetLastError();
 }
 
 }  // namespace
 
-int sketch_chunks(int64_t rows) { return (int)((rows + kSkRows - 1) / kSkRows); }
+// Rows per partial workgroup: about 1024 workgroups over the layers, heads and
+// Z (four per compute unit: their ends even out), whole load groups, at least
+// 128 rows (below that a workgroup's partial costs more than its products).
+int sketch_chunk_rows(int64_t n_tokens, int w, int n_kv_heads) {
+  const int64_t r = ((int64_t)w * n_tokens * n_kv_heads * 2 + 1023) / 1024;
+  const int64_t up = (r + kSkGroup - 1) / kSkGroup * kSkGroup;
+  return (int)(up < 128 ? 128 : up);
+}
 
 hipError_t launch_sketch(const SketchArgs& a, hipStream_t s) {
   switch (a.rb) {

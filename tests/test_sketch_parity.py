@@ -63,6 +63,28 @@ def test_sketch_small(rb, n_tok, kind):
     assert np.array_equal(after[mask], before[mask]), "another sequence's or window's basis changed"
 
 
+@pytest.mark.parametrize("rb,n_tok", [(64, 1), (48, 31), (80, 33), (112, 129), (96, 257), (128, 4129)])
+def test_sketch_chunk_edges(rb, n_tok):
+    """Prefills of one row, around a 32-row load group and a 128-row chunk, and
+    with odd and even r_b / 16 (the sketch operand's two load forms); the bar is
+    the fp16 rounding of float64 results, one step."""
+    torch = torch_gpu()
+    w = Workload(name=f"ske{rb}", batch=1, n_layers=3, window=3, n_kv_heads=2, n_q_heads=4, head_dim=128,
+                 context=64, basis_rank=rb, levels=(0, 8), probs=(0.5, 0.5), q_dtype="bf16", seed=rb)
+    dc = device_cache(generate(w, threads=4))
+    rng = np.random.default_rng(rb * 1000 + n_tok)
+    x = rng.standard_normal((3, 2, n_tok, 2, 128)).astype(np.float16)
+    omega = rng.standard_normal((3 * n_tok, rb)).astype(np.float16)
+    announce(f"sketch edges rb={rb} n={n_tok}")
+    dev = lambda a: torch.from_numpy(a).cuda()
+    dc.sketch_basis(0, 0, dev(x), dev(omega))
+    torch.cuda.synchronize()
+    after = dc.basis.cpu().numpy().view(np.float16)[0, 0]
+    for h in range(2):
+        for z in range(2):
+            _compare(after[h, z], OS.sketch_basis(x, omega, h, z), f"rb {rb} n={n_tok} h={h} z={z}")
+
+
 def test_sketch_full_size_sampled():
     torch = torch_gpu()
     host = generate(LLAMA8B_64K, layers=(0, 4), with_q=False)
