@@ -241,6 +241,36 @@ def test_compress_int8_bit_exact(case):
             compare(out, oracle.decode(ref, l), pairs, host.n_q_heads // host.n_kv_heads, f"{name} decode l={l}")
 
 
+TILE_CASES = [
+    # name, r_b, levels, probs, lengths, range, format: prompts run 16-token tiles, whose tokens with
+    # entries wait in a ring until 16 are there
+    ("tile-9-unaligned", 64, (0, 4, 16), (0.4, 0.3, 0.3), [40], (7, 16), "f16"),
+    ("tile-16", 48, (4, 8), (0.5, 0.5), [64], (16, 32), "f16"),
+    ("tile-17-unaligned", 32, (0, 8), (0.5, 0.5), [90], (15, 32), "f16"),
+    ("tile-short-seqs", 112, (0, 4, 16), (0.2, 0.4, 0.4), [3, 5, 1, 0, 9, 40, 2, 17, 1, 70], (2, 147), "f16"),
+    ("tile-short-seqs-i8", 96, (0, 4, 16), (0.2, 0.4, 0.4), [3, 5, 1, 0, 9, 40, 2, 17, 1, 70], (1, 146), "int8"),
+    ("tile-all-ranked", 16, (2, 64), (0.5, 0.5), [300, 1, 211], (3, 511), "f16"),
+    ("tile-all-ranked-i8", 80, (2, 64, 128), (0.4, 0.3, 0.3), [300, 1, 211], (0, 512), "int8"),
+    ("tile-few-ranked", 128, (0, 6), (0.97, 0.03), [700], (1, 700), "f16"),
+]
+
+
+@pytest.mark.parametrize("case", TILE_CASES, ids=[c[0] for c in TILE_CASES])
+def test_compress_tiles_bit_exact(case):
+    """The prompt kernel at the edges of its tiles and batches: ranges that start
+    and end inside a tile, several sequences in one tile, every or hardly any
+    token with entries."""
+    torch_gpu()
+    name, rb, levels, probs, lengths, (t0, t1), fmt = case
+    w = _Fixed(Workload(name=name, batch=len(lengths), n_layers=2, window=2, n_kv_heads=2, n_q_heads=4,
+                        head_dim=128, context=max(lengths), basis_rank=rb, levels=levels, probs=probs,
+                        q_dtype="bf16", seed=700 + len(name), coef_format=fmt), lengths)
+    host = generate(w, threads=4)
+    rng = np.random.default_rng(11 + len(name))
+    gate = rng.uniform(0.0, 1.0, size=(2, host.n_kv_heads, t1 - t0)).astype(np.float32)
+    _run_case(host, device_cache(host), [1], t0, t1, [_inputs(host, 1, t0, t1, "normal", rng)], [gate], None, name)
+
+
 def test_compress_zero_residual_and_ties():
     """Signed-permutation bases: inputs on the basis channels leave r = 0 exactly
     (scale 0, codes 0, channels 0..rho-1 by the tie rule); inputs with repeated
