@@ -280,7 +280,7 @@ size_t dwkv_route_budget_workspace_bytes(const dwkv_dims* dims);
  *   phi, u, rank_code, res_off: as dwkv_route (phi and u 16-byte aligned)
  *   workspace: >= dwkv_route_budget_workspace_bytes(dims), no initial contents
  * phi must be finite (a NaN score has no defined place).  Bit-exact by
- * construction.  One launch, one workgroup per (window, head). */
+ * construction.  One launch for ranges of up to 16384 tokens, else six. */
 dwkv_status dwkv_route_budget(const dwkv_dims* dims, const float* phi, const float* u, const int64_t* entries,
                               int64_t t0, int64_t t1, uint8_t* rank_code, uint32_t* res_off, void* workspace,
                               size_t ws_bytes, void* stream);

@@ -655,10 +655,33 @@ dwkv_status dwkv_route(const dwkv_dims* d, const float* phi, const float* u, con
                           ws_bytes, stream);
 }
 
+}  // extern "C"
+
+namespace {
+
+// Budget routing's workspace: score bits, digit histograms, state, block counts.
+struct BudgetWs {
+  size_t hist, state, bsum, total;
+};
+
+BudgetWs budget_ws(const dwkv_dims* d) {
+  const size_t n_mh = (size_t)(d->n_layers / d->window) * d->n_kv_heads, T = (size_t)d->total_tokens;
+  const size_t nblk = (T + kBudgetTokensPerBlock - 1) / kBudgetTokensPerBlock;
+  BudgetWs w;
+  w.hist = align_up(n_mh * T * sizeof(uint32_t), 256);
+  w.state = w.hist + align_up(n_mh * kBudgetHistWords * sizeof(uint32_t), 256);
+  w.bsum = w.state + align_up(n_mh * 4 * sizeof(uint32_t), 256);
+  w.total = w.bsum + align_up(n_mh * nblk * 2 * sizeof(uint32_t), 256);
+  return w;
+}
+
+}  // namespace
+
+extern "C" {
+
 size_t dwkv_route_budget_workspace_bytes(const dwkv_dims* d) {
   if (check_dims(d) != DWKV_OK) return 0;
-  const size_t n = (size_t)(d->n_layers / d->window) * d->n_kv_heads * (size_t)d->total_tokens * 8;
-  return n > 0 ? align_up(n, 256) : 256;
+  return budget_ws(d).total;
 }
 
 dwkv_status dwkv_route_budget(const dwkv_dims* d, const float* phi, const float* u, const int64_t* entries,
@@ -681,10 +704,16 @@ dwkv_status dwkv_route_budget(const dwkv_dims* d, const float* phi, const float*
   a.code = rank_code;
   a.off = res_off;
   a.entries = entries;
-  a.keys = static_cast<unsigned long long*>(workspace);
+  const BudgetWs bw = budget_ws(d);
+  char* ws = static_cast<char*>(workspace);
+  a.keys = reinterpret_cast<uint32_t*>(ws);
+  a.hist = reinterpret_cast<uint32_t*>(ws + bw.hist);
+  a.state = reinterpret_cast<uint32_t*>(ws + bw.state);
+  a.bsum = reinterpret_cast<uint32_t*>(ws + bw.bsum);
   a.T = d->total_tokens;
   a.t0 = t0;
   a.n = t1 - t0;
+  a.nblk = (int)((a.n + kBudgetTokensPerBlock - 1) / kBudgetTokensPerBlock);
   a.n_kv_heads = d->n_kv_heads;
   a.n_levels = d->n_levels;
   for (int i = 0; i < DWKV_MAX_LEVELS; ++i) a.levels[i] = i < d->n_levels ? d->levels[i] : 0;

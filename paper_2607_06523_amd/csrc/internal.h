@@ -260,7 +260,9 @@ struct RouteArgs {
   int64_t T;                   // token stride of code / off / phi
   int64_t t0, n;               // routed range [t0, t0 + n); off[t0] holds the carry-in
   const int64_t* entries;      // budget routing: residual entries allowed per (window, head)
-  unsigned long long* keys;    // budget routing: selection keys [M*Hkv][T]
+  uint32_t* keys;              // budget routing: order-preserving score bits [M*Hkv][T]
+  uint32_t* hist;              // budget routing: digit histograms [M*Hkv][3][2048]
+  uint32_t* state;             // budget routing: [M*Hkv][4], handed from launch to launch
   int32_t n_kv_heads;
   int32_t n_levels;
   int32_t nblk;
@@ -268,6 +270,8 @@ struct RouteArgs {
 };
 
 constexpr int kRouteTokensPerBlock = 1024;
+constexpr int kBudgetTokensPerBlock = 2048;
+constexpr int kBudgetHistWords = 3 * 2048;
 
 // Append/compress of packed tokens [t0, t0 + n) of one layer.
 struct CompressArgs {
@@ -313,8 +317,8 @@ hipError_t launch_split_tl_scores_c8(int rb, int g, bool resid, const SplitArgs&
 hipError_t launch_merge_tl(int rb, int g, const WMergeArgs& a, hipStream_t s);
 hipError_t launch_merge(const MergeArgs& a, hipStream_t s);
 hipError_t launch_route(const RouteArgs& a, int n_mh, hipStream_t s);
-// Two-level routing under a budget: a.entries [M*Hkv] (device), keys scratch
-// a.keys [M*Hkv][T]; one workgroup per (window, head).
+// Two-level routing under a budget: a.entries [M*Hkv] (device), scratch a.keys
+// [M*Hkv][T], a.hist, a.state and a.bsum [M*Hkv][nblk][2].
 hipError_t launch_route_budget(const RouteArgs& a, int n_mh, hipStream_t s);
 hipError_t launch_compress(const CompressArgs& a, hipStream_t s);
 

@@ -71,6 +71,35 @@ def test_route_budget_rank_floor_and_tail():
     _run(dc, host, wl, entries, 0, T, seed=6, label="all")
 
 
+@pytest.mark.parametrize("n,equal", [(1, False), (1025, False), (16384, False), (16385, False), (18432, True),
+                                     (18433, False), (16384, True)])
+def test_route_budget_range_edges(n, equal):
+    """Around the one-workgroup form's 16384 tokens and the spread form's
+    2048-token blocks, and with every score equal (the threshold's ties span
+    all blocks); whole numbers, so bit for bit."""
+    torch = torch_gpu()
+    wl = Workload(name="budget-edges", batch=1, n_layers=2, window=2, n_kv_heads=2, n_q_heads=4, head_dim=128,
+                  context=18500, basis_rank=16, levels=(2, 8), probs=(0.8, 0.2), q_dtype="bf16", seed=21)
+    host = generate(wl, threads=4)
+    dc = device_cache(host)
+    T = host.total_tokens
+    t0 = T - n
+    phi, u, _ = router_inputs(wl, 1, T)
+    if equal:
+        phi[:] = phi[:, :, :1]
+    dev = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()
+    for frac in (0.0, 0.31, 1.0):
+        entries = np.array([[n * 2 + 6 * int(n * frac), n * 2 + 6 * int(n * frac / 2) + 5]], np.int64)
+        codes_ref, off_ref = host.rank_code.copy(), host.res_off.copy()
+        OCt.route_budget(phi, u, entries, host.levels, t0, T, codes_ref, off_ref)
+        announce(f"route_budget n={n} equal={equal} share {frac}")
+        codes, off = dc.route_budget(dev(phi), dev(u), dev(entries), t0, T, dev(host.rank_code),
+                                     dev(host.res_off.view(np.int32)))
+        torch.cuda.synchronize()
+        assert np.array_equal(codes.cpu().numpy(), codes_ref), f"codes n={n} share {frac}"
+        assert np.array_equal(off.cpu().numpy().view(np.uint32), off_ref), f"offsets n={n} share {frac}"
+
+
 def test_route_budget_full_size():
     torch_gpu()
     wl = LLAMA8B_64K.with_(levels=(0, 16), probs=(0.9, 0.1))
