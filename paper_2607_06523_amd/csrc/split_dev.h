@@ -35,6 +35,12 @@
 //  * residual entries: one lane per entry; token of an entry from an LDS map
 //    written by the token lanes; key entries add into an LDS score buffer,
 //    value entries into an LDS d-vector per head (ds_add_f32).
+//  * the query's projection into basis space and the epilogue's B^V product run
+//    on v_mfma_f32_16x16x4_f32, so they keep float32 multiply-adds.  A chunk is
+//    few tiles per wave and LDS holds one workgroup per CU for large groups, so
+//    these ends are latency: at G 16, r_b 96, 16K tokens of 4 KV heads a decode
+//    call takes 32 us, and took 57 with one thread per row or output and the
+//    B^V rows requested only at the end.
 //  * epilogue: the 4 waves merge (m, l, a~, r) in LDS, project a~ through B^V
 //    and write one partial (o, m, l) per query head; a merge kernel combines
 //    the splits (and computes Eq. 3's error for probed heads).
@@ -616,7 +622,7 @@ __device__ __forceinline__ void split_body(const SplitArgs& a, int w, int slot, 
   // tile's coefficient fragments; last its residual entries, whose addresses
   // need the offsets.  Every load is unconditional (a wave with no tile reads
   // the chunk's last one and never uses it).
-  constexpr int NIT = (RB * 4 + kThreads - 1) / kThreads;   // q~ work items per thread
+  constexpr int NIT = (NS + NW - 1) / NW;                    // q~ row tiles per wave
   constexpr int QPT = (G * D + kThreads - 1) / kThreads;     // query elements per thread
   constexpr int BVQ = IDENT ? 1 : RB * D / 8 / kThreads;     // 16-byte B^V chunks per thread
   const int j0 = min(wv, x.ntile - 1);
@@ -637,11 +643,11 @@ __device__ __forceinline__ void split_body(const SplitArgs& a, int w, int slot, 
     const int i = min(tid + n * kThreads, G * D - 1);
     qraw[n] = a.q[((int64_t)b * a.n_q_heads + kvh * G + i / D) * D + i % D];
   }
-  if constexpr (!IDENT) {
+  if constexpr (!IDENT) {               // lane (col, grp): row col of the tile, channels 32 grp .. + 31
 #pragma unroll
     for (int n = 0; n < NIT; ++n) {
-      const int it = min(tid + n * kThreads, RB * 4 - 1);
-      const uint4* row = reinterpret_cast<const uint4*>(bk_rows + (it >> 2) * D + (it & 3) * 32);
+      const int tile = min(wv + n * NW, NS - 1);
+      const uint4* row = reinterpret_cast<const uint4*>(bk_rows + (16 * tile + col) * D + 32 * grp);
 #pragma unroll
       for (int i = 0; i < 4; ++i) rv[n][i] = row[i];
     }
@@ -651,6 +657,11 @@ __device__ __forceinline__ void split_body(const SplitArgs& a, int w, int slot, 
   load_v<RB, !IDENT>(fr, x, j0, lane);
   __builtin_amdgcn_sched_barrier(0);
   if constexpr (RESID) load_entries<TT>(ec, x, mc, lane);
+  u4v bvr[BVQ];                         // B^V rows, for the epilogue's projection
+  if constexpr (!IDENT) {
+#pragma unroll
+    for (int n = 0; n < BVQ; ++n) bvr[n] = reinterpret_cast<const u4v*>(bv_rows)[tid + n * kThreads];
+  }
   if (tid < G) sm.qmax[tid] = 0;
 #pragma unroll
   for (int n = 0; n < QPT; ++n) {
@@ -660,33 +671,30 @@ __device__ __forceinline__ void split_body(const SplitArgs& a, int w, int slot, 
   }
   __syncthreads();
   if constexpr (!IDENT) {
+    // q~ tiles on v_mfma_f32_16x16x4_f32 (16 basis rows x 16 heads, float32
+    // multiply-adds): lane group grp's k-step u is channel 32 grp + u
 #pragma unroll
     for (int n = 0; n < NIT; ++n) {
-      const int it = tid + n * kThreads;
-      if (it >= RB * 4) continue;
-      const int k = it >> 2, qq = it & 3;
-      float acc[G];
-#pragma unroll
-      for (int g = 0; g < G; ++g) acc[g] = 0.f;
+      const int tile = wv + n * NW;
+      if (tile >= NS) break;             // uniform over the wave
+      f4 acc = f4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
       for (int e = 0; e < 32; ++e) {
         const uint32_t dw = dword_at(rv[n][e >> 3], (e >> 1) & 3);
         const float xv = half_bits_to_float((uint16_t)((e & 1) ? (dw >> 16) : (dw & 0xFFFF)));
-#pragma unroll
-        for (int g = 0; g < G; ++g) acc[g] += xv * sm.qs[qq * 32 + e][g];
+        const float qv = sm.qs[32 * grp + e][G == 16 ? col : min(col, G - 1)];
+        acc = __builtin_amdgcn_mfma_f32_16x16x4f32(xv, G == 16 || col < G ? qv : 0.f, acc, 0, 0, 0);
       }
+      // lane (col, grp): q~[head col][row 16 tile + 4 grp + i]
+      float mx = 0.f;
 #pragma unroll
-      for (int g = 0; g < G; ++g) {
-        acc[g] += __shfl_xor(acc[g], 1);
-        acc[g] += __shfl_xor(acc[g], 2);
+      for (int i = 0; i < 4; ++i) {
+        if (col < G) sm.qt[col][16 * tile + 4 * grp + i] = acc[i];
+        mx = fmaxf(mx, fabsf(acc[i]));
       }
-      if (qq == 0) {
-#pragma unroll
-        for (int g = 0; g < G; ++g) {
-          sm.qt[g][k] = acc[g];
-          atomicMax(&sm.qmax[g], __float_as_int(fabsf(acc[g])));
-        }
-      }
+      mx = fmaxf(mx, __shfl_xor(mx, 16));
+      mx = fmaxf(mx, __shfl_xor(mx, 32));
+      if (grp == 0 && col < G) atomicMax(&sm.qmax[col], __float_as_int(mx));
     }
   } else {
     for (int i = tid; i < G * D; i += kThreads) {
@@ -737,6 +745,10 @@ __device__ __forceinline__ void split_body(const SplitArgs& a, int w, int slot, 
   // the last of them at once), so the loop's own waits count only the loop's
   // loads and stay exact.
   __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);
+  if constexpr (!IDENT) {               // read after the epilogue's barriers
+#pragma unroll
+    for (int n = 0; n < BVQ; ++n) reinterpret_cast<u4v*>(&sm.bvs[0][0])[tid + n * kThreads] = bvr[n];
+  }
 
   // stream the wave's tiles
   int j = wv;
@@ -746,9 +758,7 @@ __device__ __forceinline__ void split_body(const SplitArgs& a, int w, int slot, 
     if (lane == 0) ws.ex = st.ex;      // read by every thread after the epilogue's barrier
   }
 
-  // epilogue: the waves merge (B^V rows, needed only for the projection,
-  // are requested while they do), project a~ through B^V, write the partial
-  const int c_out = tid % D, par = tid / D;
+  // epilogue: the waves merge, project a~ through B^V, write the partial
   st.l += __shfl_xor(st.l, 16);
   st.l += __shfl_xor(st.l, 32);
   if (grp == 0 && col < G) {
@@ -762,11 +772,6 @@ __device__ __forceinline__ void split_body(const SplitArgs& a, int w, int slot, 
       const int g = 4 * grp + i;
       if (g < G) sm.ep_a[wv][g][16 * cb + col] = st.acc[cb][i];
     }
-  u4v bvr[BVQ];
-  if constexpr (!IDENT) {
-#pragma unroll
-    for (int n = 0; n < BVQ; ++n) bvr[n] = reinterpret_cast<const u4v*>(bv_rows)[tid + n * kThreads];
-  }
   __syncthreads();
   if (tid < G) {
     const int g = tid;
@@ -781,10 +786,6 @@ __device__ __forceinline__ void split_body(const SplitArgs& a, int w, int slot, 
     sm.mstar[g] = mx;
     sm.lstar[g] = l;
   }
-  if constexpr (!IDENT) {
-#pragma unroll
-    for (int n = 0; n < BVQ; ++n) reinterpret_cast<u4v*>(&sm.bvs[0][0])[tid + n * kThreads] = bvr[n];
-  }
   __syncthreads();
   for (int i = tid; i < G * RB; i += kThreads) {
     const int g = i / RB, k = i % RB;
@@ -794,28 +795,50 @@ __device__ __forceinline__ void split_body(const SplitArgs& a, int w, int slot, 
   }
   __syncthreads();
   float* const part_ws = a.part;
-  for (int g = par; g < G; g += kThreads / D) {
-    float o;
-    if constexpr (IDENT) {
-      o = sm.acomb[g][c_out];
-    } else {
-      o = 0.f;
-#pragma unroll 16
-      for (int k = 0; k < RB; ++k) o += sm.acomb[g][k] * half_bits_to_float(sm.bvs[k][c_out]);
-    }
-    if constexpr (RESID) {
-      for (int v = 0; v < NW; ++v) {
-        if constexpr (kFixedResid<RB, G>)
-          o += sm.sw[v][g] * (fixed_to_float(sm.w[v].racc[g][c_out]) * ldexpf(1.0f, sm.w[v].ex - kFxTopG));
-        else
-          o += sm.sw[v][g] * sm.w[v].racc[g][c_out];
+  if constexpr (IDENT) {
+    const int c_out = tid % D, par = tid / D;
+    for (int g = par; g < G; g += kThreads / D) {
+      float* dst = part_ws + (((int64_t)w * a.n_slots + slot) * G + g) * kPartStride;
+      dst[c_out] = sm.acomb[g][c_out];
+      if (c_out == 0) {
+        dst[D] = sm.mstar[g];
+        dst[D + 1] = sm.lstar[g];
       }
     }
-    float* dst = part_ws + (((int64_t)w * a.n_slots + slot) * G + g) * kPartStride;
-    dst[c_out] = o;
-    if (c_out == 0) {
-      dst[D] = sm.mstar[g];
-      dst[D + 1] = sm.lstar[g];
+  } else {
+    // o = a~ B^V on v_mfma_f32_16x16x4_f32 (heads x 16 channels per tile), the
+    // same multiply-adds over the basis rows in order as one thread per output
+#pragma unroll
+    for (int n = 0; n < D / 16 / NW; ++n) {
+      const int c = 16 * (wv + n * NW) + col;
+      f4 o = f4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll 8
+      for (int u = 0; u < RB / 4; ++u) {
+        const float av = sm.acomb[G == 16 ? col : min(col, G - 1)][4 * u + grp];
+        o = __builtin_amdgcn_mfma_f32_16x16x4f32(av, half_bits_to_float(sm.bvs[4 * u + grp][c]), o, 0, 0, 0);
+      }
+      // lane (col, grp): channel c of heads 4 grp + i
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int g = 4 * grp + i;
+        if (g >= G) continue;
+        float v = o[i];
+        if constexpr (RESID) {
+#pragma unroll
+          for (int wq = 0; wq < NW; ++wq) {
+            if constexpr (kFixedResid<RB, G>)
+              v += sm.sw[wq][g] * (fixed_to_float(sm.w[wq].racc[g][c]) * ldexpf(1.0f, sm.w[wq].ex - kFxTopG));
+            else
+              v += sm.sw[wq][g] * sm.w[wq].racc[g][c];
+          }
+        }
+        float* dst = part_ws + (((int64_t)w * a.n_slots + slot) * G + g) * kPartStride;
+        dst[c] = v;
+        if (c == 0) {
+          dst[D] = sm.mstar[g];
+          dst[D + 1] = sm.lstar[g];
+        }
+      }
     }
   }
 }
