@@ -4,15 +4,19 @@
 // comparison path (rebuild, then dense attention over the rebuilt cache), the
 // design the fused decode avoids.
 //
-// One workgroup of 2 waves takes 256 packed tokens (16 blocks of 16) of one
-// (KV head, Z).  It stages the basis of each sequence the tokens belong to in
-// LDS, transposed (channel-major, so an MFMA B fragment is one 8-byte read),
-// and the waves take alternate blocks, each computing [16 tokens x 128 channels] on
-// v_mfma_f32_16x16x16f16: coefficient rows as the A operand, basis columns as
-// B, 8 output tiles of 16 channels.  The tile goes through LDS (fp32), the
-// token's routed residual channels are added there by the token's lane, and
-// the rows are rounded to fp16 and stored: keys row-major, values in the
-// 16-token blocked layout (padding tokens of the last block zeroed).
+// Bound by HBM: a 64K layer of 8 KV heads (r_b 48) reads 108 MB and writes 268.
+// A workgroup of 4 waves stages the basis of each sequence its tokens belong to
+// in LDS, transposed (channel-major, so an MFMA fragment is one 8-byte read);
+// the waves take its 16-token blocks in turn, each [16 tokens x 128 channels]
+// on v_mfma_f32_16x16x16f16.  The operands are chosen so that a result is
+// stored from the registers it ends in (keys row-major, values in the 16-token
+// blocked layout, padding tokens of the last block zeroed); only the routed
+// residual codes go through LDS, as bytes, and are added to the float32 product
+// before the one rounding.  A block's coefficients and entries are loaded one
+// block ahead, its offsets two, and 4 waves fit a SIMD up to r_b 64.
+// Measured at that layer: the materialize + dense decode pair takes 145 us,
+// against 208 us when two-wave workgroups passed a float32 tile through LDS and
+// waited for every block's entries.
 #include "entry.h"
 #include "internal.h"
 
@@ -20,12 +24,16 @@ namespace dwkv {
 namespace {
 
 constexpr int D = kHeadDim;
-constexpr int kMW = 2;                   // waves per workgroup
-constexpr int kMTok = 256;               // tokens per workgroup (16 blocks of 16; waves alternate)
+constexpr int kMW = 4;                   // waves per workgroup
+constexpr int kMBlocks = 16;             // 16-token blocks per wave of a large launch (8: 146.1 us for the pair, 16: 145.4)
+constexpr int kMWaves = 4096;            // 4 waves on each of 1024 SIMDs
+constexpr int kMRegRank = 32;            // bases up to this rank keep their fragments in registers (at 48
+                                         // they no longer fit the 128 registers of 4 waves per SIMD)
 constexpr int kMaxEnt = 16;              // entries of a token read in one batch (4 per lane of its column)
 
 typedef _Float16 h4 __attribute__((ext_vector_type(4)));
 typedef float f4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u4 __attribute__((ext_vector_type(4)));   // not uint4, whose copies stay in scratch
 
 __device__ __forceinline__ void wave_lds_sync() {
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
@@ -51,174 +59,256 @@ template <int RB>
 struct MSmem {
   static constexpr int BT = RB + 4;      // transposed basis row (halves); the pad spreads the
                                          // 16 lanes of a fragment read over distinct banks
+  static constexpr int ST = RB * 8 + 8;  // 8 tokens' value coefficients; the pad keeps the block's
+                                         // two halves on distinct banks
+  static constexpr int KROW = D + 8;     // key codes of one token, padded the same way
   alignas(16) uint16_t bt[D * BT];       // bt[c][k] = B[k][c]
-  alignas(16) float tile[kMW][16][D + 4];
+  alignas(16) uint8_t codes[kMW][16 * KROW];    // int4 codes of a block: keys [token][c], values [c][token]
+  alignas(16) uint16_t stage[kMW][2 * ST];      // a block's value coefficients as stored
 };
 
-// Inputs of one 16-token block a wave loads ahead of its arithmetic.
-template <int RB>
-struct MBlock {
-  h4 af[RB / 16];                        // coefficient fragments of token w0 + r
-  uint32_t e0, e1;                       // entry range of token w0 + r
-  uint32_t sbits;                        // its gate-folded scale (fp16 bits)
-  uint32_t chs[kMaxEnt / 4], cbs[kMaxEnt / 4];   // entries grp + 4u: channel byte, code byte
-};
-
-// First stage: coefficients, offsets and scale of block [w0, w0+16), rows
-// [a0, a1) (zero outside).
-template <int RB>
-__device__ __forceinline__ void mat_load(MBlock<RB>& m, int64_t w0, int64_t a0, int64_t a1, int z, int lane,
-                                         const uint16_t* ck, const uint16_t* cv, const uint32_t* off,
-                                         const uint16_t* scale) {
-  constexpr int NS = RB / 16;
+// Fragment (output tile nt, k-step s) of the basis in LDS.
+template <int RB, int Z>
+__device__ __forceinline__ h4 mat_frag(const MSmem<RB>& sm, int nt, int s, int lane) {
   const int grp = lane >> 4, r = lane & 15;
-  const int64_t t = w0 + r;
-  const bool mine = t >= a0 && t < a1;
-#pragma unroll
-  for (int s = 0; s < NS; ++s) {
-    uint2 w = make_uint2(0u, 0u);
-    if (mine) {
-      if (z == 0) {
-        w = *reinterpret_cast<const uint2*>(ck + key_index(t, 16 * s + 4 * grp, RB));
-      } else {                          // 4 channels of token t, 8 elements apart
-        const uint16_t* p = cv + value_index(t, 16 * s + 4 * grp, RB);
-        w.x = (uint32_t)p[0] | ((uint32_t)p[8] << 16);
-        w.y = (uint32_t)p[16] | ((uint32_t)p[24] << 16);
-      }
-    }
-    m.af[s] = __builtin_bit_cast(h4, w);
-  }
-  m.e0 = m.e1 = 0;
-  m.sbits = 0;
-  if (mine) {
-    m.e0 = off[t];
-    m.e1 = off[t + 1];
-    m.sbits = scale[t];
-  }
+  const int c = Z == 0 ? 32 * (nt >> 1) + 8 * (r >> 2) + 4 * (nt & 1) + (r & 3) : 16 * nt + r;
+  return *reinterpret_cast<const h4*>(&sm.bt[c * MSmem<RB>::BT + 16 * s + 4 * grp]);
 }
 
-// Second stage: the block's residual entries (needs the offsets).  The four
-// lanes of a token's column share its entries: lane group grp takes entries
-// grp, grp + 4, ...
-template <int RB>
-__device__ __forceinline__ uint32_t mat_entries(MBlock<RB>& m, const MatArgs& a, const uint8_t* idx,
-                                                const uint8_t* val, int lane) {
-  const uint32_t grp = (uint32_t)lane >> 4;
-  uint32_t rho = m.e1 > m.e0 ? min(m.e1 - m.e0, (uint32_t)D) : 0u;
-  if (m.e0 + rho > (uint64_t)a.res_stride) rho = 0;    // a malformed table adds nothing
+// Offsets and scale of token w0 + r of a 16-token block.
+struct MHead {
+  uint32_t e0, rho, sbits;
+};
+
+__device__ __forceinline__ void mat_head(MHead& m, const MatArgs& a, int w0, int s0, int s1, int r,
+                                         const uint32_t* off, const uint16_t* scale) {
+  const int t = min(w0 + r, (int)a.T - 1);
+  const uint32_t e0 = off[t], e1 = off[t + 1];
+  m.sbits = scale[t];
+  m.e0 = e0;
+  m.rho = w0 + r >= s0 && w0 + r < s1 && e1 > e0 ? min(e1 - e0, (uint32_t)D) : 0u;
+  if (e0 + m.rho > (uint64_t)a.res_stride) m.rho = 0;   // a malformed table adds nothing
+}
+
+// Coefficients and residual entries of a block.  The four lanes of a token's
+// column share its entries: lane group grp takes entries grp, grp + 4, ...
+template <int RB, int Z>
+struct MBlock {
+  static constexpr int NV = (2 * RB + 63) / 64;
+  u4 raw[Z ? NV : 1];                    // values: 16-byte pieces lane, lane + 64, ... of the block
+  h4 af[Z ? 1 : RB / 16];                // keys: fragments of token w0 + r
+  uint32_t chs[kMaxEnt / 4], cbs[kMaxEnt / 4];
+};
+
+template <int RB, int Z>
+__device__ __forceinline__ void mat_load(MBlock<RB, Z>& m, const MHead& hd, int w0, int lane,
+                                         const uint16_t* coef, const uint8_t* idx, const uint8_t* val) {
+  const int grp = lane >> 4, r = lane & 15;
+  if constexpr (Z == 0) {
+#pragma unroll
+    for (int s = 0; s < RB / 16; ++s)
+      m.af[s] = *reinterpret_cast<const h4*>(coef + (int64_t)w0 * RB + key_index(r, 16 * s + 4 * grp, RB));
+  } else {
+    const u4* src = reinterpret_cast<const u4*>(coef + (int64_t)w0 * RB);
+#pragma unroll
+    for (int u = 0; u < MBlock<RB, Z>::NV; ++u) m.raw[u] = src[min(lane + 64 * u, 2 * RB - 1)];
+  }
 #pragma unroll
   for (int u = 0; u < kMaxEnt / 4; ++u) {
     const uint32_t j = grp + 4u * u;
-    m.chs[u] = j < rho ? idx[m.e0 + j] : 0u;
-    m.cbs[u] = j < rho ? val[(m.e0 + j) >> 1] : 0u;
+    m.chs[u] = m.cbs[u] = 0u;
+    if (j < hd.rho) {
+      m.chs[u] = idx[hd.e0 + j];
+      m.cbs[u] = val[(hd.e0 + j) >> 1];
+    }
   }
-  return rho;
 }
 
-// One wave, one 16-token block [w0, w0+16): rows [a0, a1) of it belong to the
-// sequence whose basis is in LDS; they are computed, completed with their
-// residual channels and stored (other rows untouched).
-template <int RB>
-__device__ __forceinline__ void mat_block(const MatArgs& a, MSmem<RB>& sm, float (*tile)[D + 4], int64_t w0,
-                                          int64_t a0, int64_t a1, int z, int lane, const MBlock<RB>& m,
-                                          uint32_t rho, const uint8_t* idx, const uint8_t* val,
-                                          uint16_t* kout, uint16_t* vout) {
+// One wave, one 16-token block [w0, w0+16): the rows [a0, a1) of it that
+// belong to the sequence whose basis is in LDS are computed, completed with
+// their residual channels, rounded once to fp16 and stored.  Keys take the
+// basis as the A operand, so a lane ends with 8 consecutive channels of one
+// token (row i of tile nt is channel 32 (nt / 2) + 8 (i / 4) + 4 (nt % 2) +
+// i % 4); values take the coefficients as A, so a lane ends with 4 consecutive
+// tokens of one channel: both store whole 64-byte and longer segments from
+// registers.
+template <int RB, int Z>
+__device__ __forceinline__ void mat_block(MSmem<RB>& sm, const h4 (&bf)[RB <= kMRegRank ? D / 16 : 1][RB / 16],
+                                          int wv, int w0, int a0, int a1, int lane,
+                                          const MBlock<RB, Z>& m, const MHead& hd, const uint8_t* idx,
+                                          const uint8_t* val, uint16_t* out) {
   constexpr int NS = RB / 16;
-  constexpr int BT = MSmem<RB>::BT;
+  constexpr int KROW = MSmem<RB>::KROW, ST = MSmem<RB>::ST;
   const int grp = lane >> 4, r = lane & 15;
-  const uint32_t e0 = m.e0;
-  const float gs = half_bits_to_float((uint16_t)m.sbits);
-  wave_lds_sync();                     // the previous block's stores have read the tile
-  // 8 output tiles of 16 channels
+  uint8_t* codes = sm.codes[wv];
+  const bool any = __any(hd.rho > 0);    // uniform
+  wave_lds_sync();                       // the previous block's reads are done
+  h4 af[NS];
+  if constexpr (Z == 0) {
 #pragma unroll
-  for (int nt = 0; nt < D / 16; ++nt) {
-    f4 acc = {0.f, 0.f, 0.f, 0.f};
+    for (int s = 0; s < NS; ++s) af[s] = m.af[s];
+  } else {
 #pragma unroll
-    for (int s = 0; s < NS; ++s) {
-      const h4 bf = *reinterpret_cast<const h4*>(&sm.bt[(16 * nt + r) * BT + 16 * s + 4 * grp]);
-      acc = __builtin_amdgcn_mfma_f32_16x16x16f16(m.af[s], bf, acc, 0, 0, 0);
+    for (int u = 0; u < MBlock<RB, Z>::NV; ++u) {
+      const int p = lane + 64 * u;
+      if (p < 2 * RB) *reinterpret_cast<u4*>(&sm.stage[wv][8 * p + (p >= RB ? 8 : 0)]) = m.raw[u];
     }
+  }
+  if (any) {
+    if constexpr (Z == 0) {
 #pragma unroll
-    for (int j = 0; j < 4; ++j) tile[4 * grp + j][16 * nt + r] = acc[j];
+      for (int u = 0; u < 4; ++u) *reinterpret_cast<uint2*>(codes + r * KROW + 32 * grp + 8 * u) = make_uint2(0u, 0u);
+    } else {
+#pragma unroll
+      for (int u = 0; u < 2; ++u) *reinterpret_cast<uint4*>(codes + 32 * lane + 16 * u) = make_uint4(0u, 0u, 0u, 0u);
+    }
   }
   wave_lds_sync();
-  // routed residual channels: the four lanes of a token's column add
-  // g*s*code at its channels (distinct channels, so no two lanes meet)
-  if (rho > 0) {
+  if (any) {                             // the channels of a token are distinct: no two lanes meet
+    auto put = [&](uint32_t ch, int q) __attribute__((always_inline)) { codes[Z == 0 ? r * KROW + (ch & (D - 1)) : (ch & (D - 1)) * 16 + r] = (uint8_t)q; };
 #pragma unroll
     for (int u = 0; u < kMaxEnt / 4; ++u) {
       const uint32_t j = (uint32_t)grp + 4u * u;
-      if (j < rho) tile[r][m.chs[u] & (D - 1)] += gs * (float)entry_code(m.cbs[u], (int64_t)(e0 + j));
+      if (j < hd.rho) put(m.chs[u], entry_code(m.cbs[u], (int64_t)(hd.e0 + j)));
     }
-    for (uint32_t j = kMaxEnt + grp; j < rho; j += 4) {   // ranks above 16
-      const uint32_t e = e0 + j;
-      tile[r][idx[e] & (D - 1)] += gs * (float)entry_code(val[e >> 1], (int64_t)e);
+    for (uint32_t j = kMaxEnt + grp; j < hd.rho; j += 4) {   // ranks above 16
+      const uint32_t e = hd.e0 + j;
+      put(idx[e], entry_code(val[e >> 1], (int64_t)e));
+    }
+  }
+  if constexpr (Z == 1) {
+    const uint16_t* st = sm.stage[wv] + (r >> 3) * ST + (r & 7);
+#pragma unroll
+    for (int s = 0; s < NS; ++s) {
+      const uint16_t* p = st + (16 * s + 4 * grp) * 8;
+      af[s] = __builtin_bit_cast(h4, make_uint2(p[0] | ((uint32_t)p[8] << 16), p[16] | ((uint32_t)p[24] << 16)));
     }
   }
   wave_lds_sync();
-  // store the rows of this sequence, rounded once to fp16
-  if (z == 0) {
-    const int tr = lane >> 2, q = lane & 3;          // token row, 32-channel quarter
-    const int64_t tt = w0 + tr;
-    if (tt >= a0 && tt < a1) {
-      uint4* dst = reinterpret_cast<uint4*>(kout + tt * D + 32 * q);
+  const float gs = half_bits_to_float((uint16_t)hd.sbits);
+  // the product of output tile nt; the basis fragments of wide bases stay in LDS
+  auto product = [&](int nt) __attribute__((always_inline)) {
+    f4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const float4 x0 = *reinterpret_cast<const float4*>(&tile[tr][32 * q + 8 * u]);
-        const float4 x1 = *reinterpret_cast<const float4*>(&tile[tr][32 * q + 8 * u + 4]);
-        dst[u] = make_uint4(pack_half2(x0.x, x0.y), pack_half2(x0.z, x0.w), pack_half2(x1.x, x1.y),
-                            pack_half2(x1.z, x1.w));
+    for (int s = 0; s < NS; ++s) {
+      const h4 b = RB <= kMRegRank ? bf[RB <= kMRegRank ? nt : 0][s] : mat_frag<RB, Z>(sm, nt, s, lane);
+      acc = Z == 0 ? __builtin_amdgcn_mfma_f32_16x16x16f16(b, af[s], acc, 0, 0, 0)
+                   : __builtin_amdgcn_mfma_f32_16x16x16f16(af[s], b, acc, 0, 0, 0);
+    }
+    return acc;
+  };
+  auto code = [](uint32_t w, int j) __attribute__((always_inline)) { return (float)(int8_t)(w >> (8 * j)); };
+  if constexpr (Z == 0) {
+    const bool mine = w0 + r >= a0 && w0 + r < a1;
+    uint16_t* dst = out + (int64_t)w0 * D + (r * D + 8 * grp);
+#pragma unroll
+    for (int q = 0; q < D / 32; ++q) {
+      f4 lo = product(2 * q), hi = product(2 * q + 1);
+      if (any) {
+        const uint2 w = *reinterpret_cast<const uint2*>(codes + r * KROW + 32 * q + 8 * grp);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          lo[j] += gs * code(w.x, j);
+          hi[j] += gs * code(w.y, j);
+        }
       }
+      if (mine)
+        *reinterpret_cast<uint4*>(dst + 32 * q) = make_uint4(pack_half2(lo[0], lo[1]), pack_half2(lo[2], lo[3]),
+                                                             pack_half2(hi[0], hi[1]), pack_half2(hi[2], hi[3]));
     }
   } else {
     const bool full = a0 == w0 && a1 == w0 + 16;
+    float g4[4];                         // scales of tokens 4 grp ..
 #pragma unroll
-    for (int cc = 0; cc < 2; ++cc) {
-      const int c = 2 * lane + cc;
-      uint16_t* dst = vout + ((w0 >> 4) * D + c) * 16;
+    for (int j = 0; j < 4; ++j) g4[j] = __shfl(gs, 4 * grp + j);
+#pragma unroll
+    for (int nt = 0; nt < D / 16; ++nt) {
+      const int c = 16 * nt + r;
+      f4 x = product(nt);
+      if (any) {
+        const uint32_t w = *reinterpret_cast<const uint32_t*>(codes + 16 * c + 4 * grp);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) x[j] += g4[j] * code(w, j);
+      }
+      uint16_t* dst = out + (int64_t)w0 * D + (c * 16 + 4 * grp);
       if (full) {
-        uint32_t pk[8];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) pk[u] = pack_half2(tile[2 * u][c], tile[2 * u + 1][c]);
-        reinterpret_cast<uint4*>(dst)[0] = make_uint4(pk[0], pk[1], pk[2], pk[3]);
-        reinterpret_cast<uint4*>(dst)[1] = make_uint4(pk[4], pk[5], pk[6], pk[7]);
+        *reinterpret_cast<uint2*>(dst) = make_uint2(pack_half2(x[0], x[1]), pack_half2(x[2], x[3]));
       } else {
-        for (int64_t tt = a0; tt < a1; ++tt)
-          dst[tt - w0] = __builtin_bit_cast(uint16_t, (_Float16)tile[tt - w0][c]);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          const int t = w0 + 4 * grp + j;
+          if (t >= a0 && t < a1) dst[j] = __builtin_bit_cast(uint16_t, (_Float16)x[j]);
+        }
       }
     }
   }
 }
 
-// grid (ceil(T16 / 256), Hkv, 2)
+// Blocks i0..i1 of the workgroup (16 tokens from g0 + 16 i), dealt to the waves
+// in turn; block i's coefficients and entries are loaded one turn ahead and its
+// offsets, which the entries wait for, two.
+template <int RB, int Z>
+__device__ __forceinline__ void mat_rows(const MatArgs& a, MSmem<RB>& sm, int wv, int lane, int g0, int s0, int s1,
+                                         const uint16_t* coef, const uint32_t* off, const uint16_t* scale,
+                                         const uint8_t* idx, const uint8_t* val, uint16_t* out) {
+  const int r = lane & 15;
+  const int b0 = (s0 - g0) >> 4, b1 = (s1 - 1 - g0) >> 4;
+  int i = b0 + ((wv - b0) % kMW + kMW) % kMW;
+  if (i > b1) return;
+  h4 bf[RB <= kMRegRank ? D / 16 : 1][RB / 16];
+  if constexpr (RB <= kMRegRank) {
+#pragma unroll
+    for (int nt = 0; nt < D / 16; ++nt)
+#pragma unroll
+      for (int s = 0; s < RB / 16; ++s) bf[nt][s] = mat_frag<RB, Z>(sm, nt, s, lane);
+  }
+  // past the wave's last block the loads repeat it
+  const int last = i + (b1 - i) / kMW * kMW;
+  auto tok = [&](int b) __attribute__((always_inline)) { return g0 + 16 * min(b, last); };
+  MHead h0, h1;
+  MBlock<RB, Z> cur;
+  mat_head(h0, a, tok(i), s0, s1, r, off, scale);
+  mat_head(h1, a, tok(i + kMW), s0, s1, r, off, scale);
+  mat_load<RB, Z>(cur, h0, tok(i), lane, coef, idx, val);
+  for (; i <= b1; i += kMW) {
+    MHead h2;
+    MBlock<RB, Z> nxt;
+    mat_head(h2, a, tok(i + 2 * kMW), s0, s1, r, off, scale);
+    mat_load<RB, Z>(nxt, h1, tok(i + kMW), lane, coef, idx, val);
+    const int w0 = g0 + 16 * i;
+    mat_block<RB, Z>(sm, bf, wv, w0, max(s0, w0), min(s1, w0 + 16), lane, cur, h0, idx, val, out);
+    cur = nxt;
+    h0 = h1;
+    h1 = h2;
+  }
+}
+
+// grid (ceil(T16 / tokens per workgroup), Hkv, 2)
 template <int RB>
-__global__ __launch_bounds__(kMW * 64) void materialize_kernel(const MatArgs a) {
+__global__ __launch_bounds__(kMW * 64, RB <= 64 ? 4 : RB < 128 ? 3 : 2) void materialize_kernel(const MatArgs a) {
   constexpr int BT = MSmem<RB>::BT;
   __shared__ MSmem<RB> sm;
   const int h = blockIdx.y, z = blockIdx.z;
-  const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int64_t T = a.T;
-  const int64_t g0 = (int64_t)blockIdx.x * kMTok;         // a multiple of 16
-  const int64_t gend = min(g0 + (int64_t)kMTok, T);
+  const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const int T = (int)a.T;                // below 2^31: cu_seqlens are 32-bit
+  const int g0 = blockIdx.x * a.wg_tokens;                // a multiple of 16
+  const int gend = (int)min((int64_t)g0 + a.wg_tokens, a.T);
   const int64_t slab = (int64_t)z * a.n_kv_heads + h;
-  const uint16_t* ck = a.coef_k + (int64_t)h * a.T16 * RB;
-  const uint16_t* cv = a.coef_v + (int64_t)h * a.T16 * RB;
-  const uint32_t* off = a.off + (int64_t)h * (T + 1);
+  const uint16_t* coef = (z ? a.coef_v : a.coef_k) + (int64_t)h * a.T16 * RB;
+  const uint32_t* off = a.off + (int64_t)h * (a.T + 1);
   const uint8_t* idx = a.idx + slab * a.res_stride;
   const uint8_t* val = a.val + slab * (a.res_stride / 2);
-  const uint16_t* scale = a.scale + slab * T;
-  uint16_t* kout = a.k_out + (int64_t)h * T * D;
-  uint16_t* vout = a.v_out + (int64_t)h * a.T16 * D;
-  float (*tile)[D + 4] = sm.tile[wv];
+  const uint16_t* scale = a.scale + slab * a.T;
+  uint16_t* out = z ? a.v_out + (int64_t)h * a.T16 * D : a.k_out + (int64_t)h * a.T * D;
 
   if (g0 < T) {
-    for (int b = seq_of(a.cu, a.batch, g0); b < a.batch && (int64_t)a.cu[b] < gend; ++b) {
-      const int64_t s0 = max(g0, (int64_t)a.cu[b]), s1 = min(gend, (int64_t)a.cu[b + 1]);
+    for (int b = seq_of(a.cu, a.batch, g0); b < a.batch && a.cu[b] < gend; ++b) {
+      const int s0 = max(g0, a.cu[b]), s1 = min(gend, a.cu[b + 1]);
       if (s1 <= s0) continue;            // empty sequence (uniform)
-      __syncthreads();                   // both waves are done with the previous basis
+      __syncthreads();                   // every wave is done with the previous basis
       const uint16_t* src = a.basis + (int64_t)b * a.basis_b_stride + (int64_t)(h * 2 + z) * RB * D;
       for (int e = threadIdx.x; e < RB * (D / 8); e += kMW * 64) {
-        const int k = e / (D / 8), c8 = e % (D / 8);
+        const int k = e % RB, c8 = e / RB;   // lanes along k: the 2-byte writes of a wave are contiguous
         const uint4 w = *reinterpret_cast<const uint4*>(src + (int64_t)k * D + 8 * c8);
         const uint32_t ws[4] = {w.x, w.y, w.z, w.w};
 #pragma unroll
@@ -226,44 +316,32 @@ __global__ __launch_bounds__(kMW * 64) void materialize_kernel(const MatArgs a) 
           sm.bt[(8 * c8 + u) * BT + k] = (uint16_t)(ws[u >> 1] >> (16 * (u & 1)));
       }
       __syncthreads();
-      // block i of the workgroup (16 tokens from g0 + 16 i) belongs to wave i % kMW;
-      // the next block's inputs are loaded while this one computes
-      const int64_t i0 = (s0 - g0) >> 4, i1 = (s1 - 1 - g0) >> 4;
-      int64_t i = i0 + ((wv - i0) % kMW + kMW) % kMW;
-      if (i <= i1) {
-        MBlock<RB> cur, nxt;
-        int64_t w0 = g0 + 16 * i;
-        mat_load<RB>(cur, w0, max(s0, w0), min(s1, w0 + 16), z, lane, ck, cv, off, scale);
-        uint32_t rho = mat_entries<RB>(cur, a, idx, val, lane);
-        for (; i <= i1; i += kMW) {
-          w0 = g0 + 16 * i;
-          const int64_t wn = w0 + 16 * kMW;
-          const bool more = i + kMW <= i1;
-          if (more) mat_load<RB>(nxt, wn, max(s0, wn), min(s1, wn + 16), z, lane, ck, cv, off, scale);
-          mat_block<RB>(a, sm, tile, w0, max(s0, w0), min(s1, w0 + 16), z, lane, cur, rho, idx, val, kout, vout);
-          if (more) {
-            cur = nxt;
-            rho = mat_entries<RB>(cur, a, idx, val, lane);
-          }
-        }
-      }
+      if (z == 0)
+        mat_rows<RB, 0>(a, sm, wv, lane, g0, s0, s1, coef, off, scale, idx, val, out);
+      else
+        mat_rows<RB, 1>(a, sm, wv, lane, g0, s0, s1, coef, off, scale, idx, val, out);
     }
   }
   // value padding of the last block: tokens [T, T16) are zero
-  if (z == 1 && T < a.T16) {
+  if (z == 1 && T < a.T16 && wv == 0) {
     const int64_t wl = a.T16 - 16;
-    if (wl >= g0 && wl < g0 + kMTok && ((wl - g0) >> 4) % kMW == wv) {
+    if (wl >= g0 && wl < (int64_t)g0 + a.wg_tokens) {
       for (int c = lane; c < D; c += 64) {
-        uint16_t* dst = vout + ((wl >> 4) * D + c) * 16;
-        for (int64_t tt = T; tt < wl + 16; ++tt) dst[tt - wl] = 0;
+        uint16_t* dst = out + ((wl >> 4) * D + c) * 16;
+        for (int64_t tt = a.T; tt < wl + 16; ++tt) dst[tt - wl] = 0;
       }
     }
   }
 }
 
 template <int RB>
-hipError_t launch_mat(const MatArgs& a, hipStream_t s) {
-  const unsigned nb = (unsigned)((a.T16 + kMTok - 1) / kMTok);
+hipError_t launch_mat(const MatArgs& in, hipStream_t s) {
+  MatArgs a = in;
+  // Each wave takes kMBlocks blocks, fewer where that would leave the chip's
+  // kMWaves resident waves idle: staging the basis then costs less than idle waves.
+  const int64_t blocks = a.T16 / 16 * a.n_kv_heads * 2;
+  a.wg_tokens = 16 * kMW * (int32_t)max((int64_t)1, min((int64_t)kMBlocks, blocks / kMWaves));
+  const unsigned nb = (unsigned)((a.T16 + a.wg_tokens - 1) / a.wg_tokens);
   hipLaunchKernelGGL(materialize_kernel<RB>, dim3(nb, a.n_kv_heads, 2), dim3(kMW * 64), 0, s, a);
   return hipGetLastError();
 }

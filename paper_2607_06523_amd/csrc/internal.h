@@ -363,6 +363,7 @@ struct MatArgs {
   uint16_t* v_out;             // [Hkv][T16/16][d][16]
   int64_t T, T16, res_stride;
   int32_t batch, n_kv_heads, rb;
+  int32_t wg_tokens;           // tokens per workgroup (launch_materialize)
 };
 hipError_t launch_materialize(const MatArgs& a, hipStream_t s);
 

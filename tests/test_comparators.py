@@ -121,6 +121,30 @@ def test_materialize_and_unfused(case):
                 assert np.all(out[b] == 0), "empty sequence must give zeros"
 
 
+# r_b and lengths per workgroup size: launches of few blocks take one block per wave (64 tokens a
+# workgroup), 8 heads of 10K tokens two (128); r_b 32 and 48 keep the basis in registers and in LDS,
+# and rank 32 has entries past the 16 loaded ahead
+EDGES = [
+    ("rb32-one-token-block", 32, 2, (0, 8, 32), (0.3, 0.4, 0.3), [1, 15, 16, 17, 32]),
+    ("rb48-one-workgroup", 48, 2, (0, 8, 32), (0.3, 0.4, 0.3), [64, 63, 1, 128]),
+    ("rb64-second-block", 64, 8, (0, 4), (0.5, 0.5), [8191, 2050]),
+    ("rb96-straddled-workgroups", 96, 8, (4, 16), (0.5, 0.5), [127, 10001, 120]),
+    ("rb112-tail", 112, 2, (0, 16), (0.9, 0.1), [321]),
+]
+
+
+@pytest.mark.parametrize("case", EDGES, ids=[c[0] for c in EDGES])
+def test_materialize_block_edges(case):
+    torch = torch_gpu()
+    name, rb, heads, levels, probs, lengths = case
+    w = _Fixed(Workload(name=name, batch=len(lengths), n_layers=1, window=1, n_kv_heads=heads, n_q_heads=heads,
+                        head_dim=128, context=max(lengths), basis_rank=rb, levels=levels, probs=probs,
+                        q_dtype="f16", seed=900 + len(name)), lengths)
+    host = generate(w, threads=4)
+    _check_materialized(host, device_cache(host), 0, name)
+    torch.cuda.synchronize()
+
+
 def test_dense_decode_random_cache():
     """A dense fp16 cache that is not a rebuilt one (N(0,1) keys and values)."""
     torch = torch_gpu()
