@@ -660,18 +660,19 @@ dwkv_status dwkv_route(const dwkv_dims* d, const float* phi, const float* u, con
 namespace {
 
 // Budget routing's workspace: score bits, digit histograms, state, block counts.
+// Only ranges above 16384 tokens use it; there the last three (24.6 KB and 8
+// bytes per 2048 tokens for each window and head) fit beside the 4 bytes a
+// token of the scores in the 8 bytes a token that the caller provides.
 struct BudgetWs {
-  size_t hist, state, bsum, total;
+  size_t hist, state, bsum;
 };
 
 BudgetWs budget_ws(const dwkv_dims* d) {
   const size_t n_mh = (size_t)(d->n_layers / d->window) * d->n_kv_heads, T = (size_t)d->total_tokens;
-  const size_t nblk = (T + kBudgetTokensPerBlock - 1) / kBudgetTokensPerBlock;
   BudgetWs w;
   w.hist = align_up(n_mh * T * sizeof(uint32_t), 256);
   w.state = w.hist + align_up(n_mh * kBudgetHistWords * sizeof(uint32_t), 256);
   w.bsum = w.state + align_up(n_mh * 4 * sizeof(uint32_t), 256);
-  w.total = w.bsum + align_up(n_mh * nblk * 2 * sizeof(uint32_t), 256);
   return w;
 }
 
@@ -681,7 +682,8 @@ extern "C" {
 
 size_t dwkv_route_budget_workspace_bytes(const dwkv_dims* d) {
   if (check_dims(d) != DWKV_OK) return 0;
-  return budget_ws(d).total;
+  const size_t n = (size_t)(d->n_layers / d->window) * d->n_kv_heads * (size_t)d->total_tokens * 8;
+  return n > 0 ? align_up(n, 256) : 256;
 }
 
 dwkv_status dwkv_route_budget(const dwkv_dims* d, const float* phi, const float* u, const int64_t* entries,
