@@ -948,9 +948,7 @@ dwkv_status dwkv_residual_map(const dwkv_dims* d, const dwkv_cache* c, int32_t l
 size_t dwkv_sketch_workspace_bytes(const dwkv_dims* d, int64_t n_tokens) {
   if (check_dims(d) != DWKV_OK || n_tokens < 1) return 0;
   const size_t row = (size_t)d->n_kv_heads * 2 * d->basis_rank * kHeadDim * sizeof(double);
-  const int64_t rows = sketch_chunk_rows(n_tokens, d->window, d->n_kv_heads);
-  const size_t chunks = (size_t)d->window * (size_t)((n_tokens + rows - 1) / rows);
-  return align_up(chunks * row, 256) + align_up(row, 256);
+  return align_up((size_t)sketch_chunks((int64_t)d->window * n_tokens) * row, 256) + align_up(row, 256);
 }
 
 dwkv_status dwkv_sketch_basis(const dwkv_dims* d, const dwkv_cache* c, int32_t window, int32_t seq,
@@ -969,9 +967,7 @@ dwkv_status dwkv_sketch_basis(const dwkv_dims* d, const dwkv_cache* c, int32_t w
   std::memset(&a, 0, sizeof(a));
   a.x = static_cast<const uint16_t*>(x);
   a.omega = static_cast<const uint16_t*>(omega);
-  a.chunk_rows = sketch_chunk_rows(n_tokens, d->window, d->n_kv_heads);
-  a.layer_chunks = (int32_t)((n_tokens + a.chunk_rows - 1) / a.chunk_rows);
-  a.n_chunks = d->window * a.layer_chunks;
+  a.n_chunks = sketch_chunks((int64_t)d->window * n_tokens);
   a.part = static_cast<double*>(workspace);
   a.q = reinterpret_cast<double*>(static_cast<char*>(workspace) +
                                   align_up((size_t)a.n_chunks * Hk * 2 * rb * kHeadDim * sizeof(double), 256));

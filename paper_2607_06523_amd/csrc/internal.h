@@ -402,10 +402,9 @@ struct SketchArgs {
   double* q;                   // [Hkv][2][rb][d] the sketch rows Y (chunk partials summed)
   uint16_t* basis;             // the (sequence, window)'s basis [Hkv][2][rb][d], written
   int64_t n_tokens;
-  int32_t w, n_kv_heads, rb;
-  int32_t chunk_rows, layer_chunks, n_chunks;   // a chunk is chunk_rows tokens of one layer
+  int32_t w, n_kv_heads, rb, n_chunks;
 };
-int sketch_chunk_rows(int64_t n_tokens, int w, int n_kv_heads);
+int sketch_chunks(int64_t rows);
 hipError_t launch_sketch(const SketchArgs& a, hipStream_t s);
 hipError_t launch_residual_map(const uint32_t* off, const uint8_t* idx, const uint8_t* val,
                                const uint16_t* scale, int64_t t0, int64_t t1, int64_t slab_len,

@@ -6,7 +6,7 @@
 //
 // Three launches:
 //  1. split-K sketch partials on v_mfma_f64_16x16x4_f64 (fp16 products are
-//     exact in float64), one workgroup per (row chunk of one layer, head, Z),
+//     exact in float64), one workgroup per (4096-row chunk, head, Z),
 //     each of its 4 waves owning 32 channels and every row of Omega.  Bound by
 //     the float64 matrix rate: the 51.5 GFLOP of a 4 x 64K window (r_b 48, 8
 //     heads) take 0.87 ms, 59 TFLOP/s of the published 78.6; one thread per
@@ -28,6 +28,7 @@ namespace {
 
 constexpr int D = kHeadDim;
 constexpr int kSkWaves = 4;                     // waves of a partial workgroup
+constexpr int kSkRowsPerChunk = 4096;           // sketch rows of a partial (the workspace holds one per 4096)
 constexpr int kSkU = 8;                         // 4-row MFMA steps per load group
 constexpr int kSkGroup = 4 * kSkU;              // rows per load group
 constexpr int kOrthWaves = 16;
@@ -81,7 +82,7 @@ __device__ __forceinline__ void sk_mma(d4 (&acc)[NS][2], const SkRows<NS>& f) {
   }
 }
 
-// grid (w * chunks per layer, Hkv, 2).  Of the MFMA operands, lane (r, kk) =
+// grid (chunks, Hkv, 2); a chunk runs over the layers that its rows lie in.  Of the MFMA operands, lane (r, kk) =
 // (lane % 16, lane / 16) holds row r (A) or column r (B) at depth kk, and the
 // result's rows 4 i + kk of column r.  Operand rows and columns are dealt so
 // that a lane's loads are contiguous: A row r of tile s is Omega entry
@@ -92,27 +93,30 @@ __global__ __launch_bounds__(64 * kSkWaves) void sketch_partial_kernel(const Ske
   const int chunk = blockIdx.x, h = blockIdx.y, z = blockIdx.z;
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
   const int r = lane & 15, kk = lane >> 4;
-  const int l = chunk / a.layer_chunks;
-  const int64_t t0 = (int64_t)(chunk % a.layer_chunks) * a.chunk_rows;
-  const int rows = (int)min((int64_t)a.chunk_rows, a.n_tokens - t0);
-  const int64_t xstride = (int64_t)a.n_kv_heads * D;
-  const uint16_t* x = a.x + (((int64_t)l * 2 + z) * a.n_tokens + t0) * xstride + (int64_t)h * D + 32 * wv + 2 * r;
-  const uint16_t* om = a.omega + ((int64_t)l * a.n_tokens + t0) * RB + NS * r;
+  const int64_t n = a.n_tokens, xstride = (int64_t)a.n_kv_heads * D;
+  const int64_t first = (int64_t)chunk * kSkRowsPerChunk, end = min(first + kSkRowsPerChunk, a.w * n);
   d4 acc[NS][2];
 #pragma unroll
   for (int s = 0; s < NS; ++s) acc[s][0] = acc[s][1] = d4{0.0, 0.0, 0.0, 0.0};
-  const int full = rows / kSkGroup;             // the next group's loads run under this one's products
-  SkRows<NS> cur, nxt;
-  if (full > 0) sk_load<NS, false>(cur, x, om, 0, rows, xstride, kk);
-  for (int g = 0; g + 1 < full; ++g) {
-    sk_load<NS, false>(nxt, x, om, (g + 1) * kSkGroup, rows, xstride, kk);
-    sk_mma<NS>(acc, cur);
-    cur = nxt;
-  }
-  if (full > 0) sk_mma<NS>(acc, cur);
-  if (rows % kSkGroup) {
-    sk_load<NS, true>(cur, x, om, full * kSkGroup, rows, xstride, kk);
-    sk_mma<NS>(acc, cur);
+  for (int64_t row = first; row < end;) {
+    const int64_t l = row / n, t0 = row - l * n;
+    const int rows = (int)min(end - row, n - t0);
+    const uint16_t* x = a.x + ((l * 2 + z) * n + t0) * xstride + (int64_t)h * D + 32 * wv + 2 * r;
+    const uint16_t* om = a.omega + row * RB + NS * r;
+    const int full = rows / kSkGroup;           // the next group's loads run under this one's products
+    SkRows<NS> cur, nxt;
+    if (full > 0) sk_load<NS, false>(cur, x, om, 0, rows, xstride, kk);
+    for (int g = 0; g + 1 < full; ++g) {
+      sk_load<NS, false>(nxt, x, om, (g + 1) * kSkGroup, rows, xstride, kk);
+      sk_mma<NS>(acc, cur);
+      cur = nxt;
+    }
+    if (full > 0) sk_mma<NS>(acc, cur);
+    if (rows % kSkGroup) {
+      sk_load<NS, true>(cur, x, om, full * kSkGroup, rows, xstride, kk);
+      sk_mma<NS>(acc, cur);
+    }
+    row += rows;
   }
   double* out = a.part + (((int64_t)chunk * a.n_kv_heads + h) * 2 + z) * RB * D + 32 * wv + 2 * r;
 #pragma unroll
@@ -224,14 +228,7 @@ hipError_t launch_sketch_rb(const SketchArgs& a, hipStream_t s) {
 
 }  // namespace
 
-// Rows per partial workgroup: about 1024 workgroups over the layers, heads and
-// Z (four per compute unit: their ends even out), whole load groups, at least
-// 128 rows (below that a workgroup's partial costs more than its products).
-int sketch_chunk_rows(int64_t n_tokens, int w, int n_kv_heads) {
-  const int64_t r = ((int64_t)w * n_tokens * n_kv_heads * 2 + 1023) / 1024;
-  const int64_t up = (r + kSkGroup - 1) / kSkGroup * kSkGroup;
-  return (int)(up < 128 ? 128 : up);
-}
+int sketch_chunks(int64_t rows) { return (int)((rows + kSkRowsPerChunk - 1) / kSkRowsPerChunk); }
 
 hipError_t launch_sketch(const SketchArgs& a, hipStream_t s) {
   switch (a.rb) {
