@@ -12,8 +12,10 @@
 // stored from the registers it ends in (keys row-major, values in the 16-token
 // blocked layout, padding tokens of the last block zeroed); only the routed
 // residual codes go through LDS, as bytes, and are added to the float32 product
-// before the one rounding.  A block's coefficients and entries are loaded one
-// block ahead, its offsets two, and 4 waves fit a SIMD up to r_b 64.
+// before the one rounding.  They are added at every channel, 0 where there is no
+// entry, which holds for finite scales only: entries of other scales follow
+// behind the wave's blocks (mat_odd).  A block's coefficients and entries are
+// loaded one block ahead, its offsets two, and 4 waves fit a SIMD up to r_b 64.
 // Measured at that layer: the materialize + dense decode pair takes 145 us,
 // against 208 us when two-wave workgroups passed a float32 tile through LDS and
 // waited for every block's entries.
@@ -90,6 +92,8 @@ __device__ __forceinline__ void mat_head(MHead& m, const MatArgs& a, int w0, int
   if (e0 + m.rho > (uint64_t)a.res_stride) m.rho = 0;   // a malformed table adds nothing
 }
 
+__device__ __forceinline__ bool scale_finite(const MHead& m) { return (m.sbits & 0x7c00u) != 0x7c00u; }
+
 // Coefficients and residual entries of a block.  The four lanes of a token's
 // column share its entries: lane group grp takes entries grp, grp + 4, ...
 template <int RB, int Z>
@@ -165,7 +169,10 @@ __device__ __forceinline__ void mat_block(MSmem<RB>& sm, const h4 (&bf)[RB <= kM
   }
   wave_lds_sync();
   if (any) {                             // the channels of a token are distinct: no two lanes meet
-    auto put = [&](uint32_t ch, int q) __attribute__((always_inline)) { codes[Z == 0 ? r * KROW + (ch & (D - 1)) : (ch & (D - 1)) * 16 + r] = (uint8_t)q; };
+    auto put = [&](uint32_t ch, int q) __attribute__((always_inline)) {
+      ch &= D - 1;
+      codes[Z == 0 ? r * KROW + ch : ch * 16 + r] = (uint8_t)q;
+    };
 #pragma unroll
     for (int u = 0; u < kMaxEnt / 4; ++u) {
       const uint32_t j = (uint32_t)grp + 4u * u;
@@ -185,7 +192,8 @@ __device__ __forceinline__ void mat_block(MSmem<RB>& sm, const h4 (&bf)[RB <= kM
     }
   }
   wave_lds_sync();
-  const float gs = half_bits_to_float((uint16_t)hd.sbits);
+  // channels without an entry take code 0, so the scale has to be finite here
+  const float gs = scale_finite(hd) ? half_bits_to_float((uint16_t)hd.sbits) : 0.f;
   // the product of output tile nt; the basis fragments of wide bases stay in LDS
   auto product = [&](int nt) __attribute__((always_inline)) {
     f4 acc = {0.f, 0.f, 0.f, 0.f};
@@ -244,6 +252,29 @@ __device__ __forceinline__ void mat_block(MSmem<RB>& sm, const h4 (&bf)[RB <= kM
   }
 }
 
+// Entries of a block's tokens whose scale is not finite, which mat_block leaves
+// out: each one's product again (all that matters of it is whether it is finite),
+// the sum stored over what the wave stored before.  Lanes share a token's
+// entries as in MBlock.
+template <int RB, int Z>
+__device__ __forceinline__ void mat_odd(const MSmem<RB>& sm, int w0, int lane, const MHead& hd, const uint16_t* coef,
+                                        const uint8_t* idx, const uint8_t* val, uint16_t* out) {
+  const int r = lane & 15;
+  if (scale_finite(hd)) return;
+  const float gs = half_bits_to_float((uint16_t)hd.sbits);
+  for (uint32_t j = lane >> 4; j < hd.rho; j += 4) {
+    const uint32_t e = hd.e0 + j;
+    const int c = idx[e] & (D - 1);
+    float x = 0.f;
+#pragma unroll 1
+    for (int k = 0; k < RB; ++k)
+      x += half_bits_to_float(coef[(int64_t)w0 * RB + (Z == 0 ? key_index(r, k, RB) : value_index(r, k, RB))]) *
+           half_bits_to_float(sm.bt[c * MSmem<RB>::BT + k]);
+    x += gs * (float)entry_code(val[e >> 1], (int64_t)e);
+    out[(int64_t)w0 * D + (Z == 0 ? r * D + c : c * 16 + r)] = __builtin_bit_cast(uint16_t, (_Float16)x);
+  }
+}
+
 // Blocks i0..i1 of the workgroup (16 tokens from g0 + 16 i), dealt to the waves
 // in turn; block i's coefficients and entries are loaded one turn ahead and its
 // offsets, which the entries wait for, two.
@@ -253,7 +284,8 @@ __device__ __forceinline__ void mat_rows(const MatArgs& a, MSmem<RB>& sm, int wv
                                          const uint8_t* idx, const uint8_t* val, uint16_t* out) {
   const int r = lane & 15;
   const int b0 = (s0 - g0) >> 4, b1 = (s1 - 1 - g0) >> 4;
-  int i = b0 + ((wv - b0) % kMW + kMW) % kMW;
+  const int first = b0 + ((wv - b0) % kMW + kMW) % kMW;
+  int i = first;
   if (i > b1) return;
   h4 bf[RB <= kMRegRank ? D / 16 : 1][RB / 16];
   if constexpr (RB <= kMRegRank) {
@@ -265,6 +297,7 @@ __device__ __forceinline__ void mat_rows(const MatArgs& a, MSmem<RB>& sm, int wv
   // past the wave's last block the loads repeat it
   const int last = i + (b1 - i) / kMW * kMW;
   auto tok = [&](int b) __attribute__((always_inline)) { return g0 + 16 * min(b, last); };
+  bool odd = false;                      // uniform
   MHead h0, h1;
   MBlock<RB, Z> cur;
   mat_head(h0, a, tok(i), s0, s1, r, off, scale);
@@ -277,9 +310,17 @@ __device__ __forceinline__ void mat_rows(const MatArgs& a, MSmem<RB>& sm, int wv
     mat_load<RB, Z>(nxt, h1, tok(i + kMW), lane, coef, idx, val);
     const int w0 = g0 + 16 * i;
     mat_block<RB, Z>(sm, bf, wv, w0, max(s0, w0), min(s1, w0 + 16), lane, cur, h0, idx, val, out);
+    odd |= __any(h0.rho > 0 && !scale_finite(h0));
     cur = nxt;
     h0 = h1;
     h1 = h2;
+  }
+  if (odd) {                             // behind the loop, whose registers are full: the lane is taken anew
+    const int ln = (int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
+    for (i = first; i <= b1; i += kMW) {
+      mat_head(h0, a, g0 + 16 * i, s0, s1, ln & 15, off, scale);
+      mat_odd<RB, Z>(sm, g0 + 16 * i, ln, h0, coef, idx, val, out);
+    }
   }
 }
 

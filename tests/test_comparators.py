@@ -145,6 +145,38 @@ def test_materialize_block_edges(case):
     torch.cuda.synchronize()
 
 
+@pytest.mark.parametrize("case", [CASES[1], EDGES[0][:2] + (2,) + EDGES[0][3:]], ids=["rb48", "rb32"])
+def test_materialize_scales_not_finite(case):
+    """A scale that is infinite or not a number reaches the token's own entries
+    and nothing else: not its other channels, not a rank-0 token's row."""
+    torch = torch_gpu()
+    host = _small(case)
+    rng = np.random.default_rng(21)
+    pick = rng.integers(0, 8, size=host.res_scale.shape)
+    for k, v in enumerate((np.inf, -np.inf, np.nan)):
+        host.res_scale[pick == k] = v
+    dc = device_cache(host)
+    announce(f"materialize, scales not finite, r_b {host.basis_rank}")
+    k_dev, v_dev = dc.materialize(1)
+    torch.cuda.synchronize()
+    got = (k_dev.cpu().numpy(), unblock_values(v_dev.cpu().numpy(), host.total_tokens))
+    odd = 0
+    for z, h, b in np.ndindex(2, host.n_kv_heads, host.batch):
+        t0, t1 = int(host.cu_seqlens[b]), int(host.cu_seqlens[b + 1])
+        with np.errstate(invalid="ignore"):
+            A = oracle.factorized.coefficient_rows(host, 1, z, h, t0, t1)
+            R = oracle.residual_map(host, 1, z, h, t0, t1)          # entries only: no 0 times infinity elsewhere
+            ref = A @ host.basis[b, 1 // host.window, h, z].astype(np.float64) + R
+            g = got[z][h, t0:t1].astype(np.float64)
+            fin = np.isfinite(ref)
+            odd += int((~fin).sum())
+            assert np.array_equal(ref[~fin], g[~fin], equal_nan=True), f"z={z} h={h} b={b}"
+            # the bound of _check_materialized (no term of a finite element is infinite)
+            tol = np.abs(ref) * 2.0 ** -11 + _abs_terms(host, 1, z, h, b) * 2.0 ** -21 + 2.0 ** -24
+            assert np.all(np.abs(g - ref)[fin] <= tol[fin]), f"z={z} h={h} b={b}"
+    assert odd > 0
+
+
 def test_dense_decode_random_cache():
     """A dense fp16 cache that is not a rebuilt one (N(0,1) keys and values)."""
     torch = torch_gpu()
