@@ -271,6 +271,34 @@ def test_compress_tiles_bit_exact(case):
     _run_case(host, device_cache(host), [1], t0, t1, [_inputs(host, 1, t0, t1, "normal", rng)], [gate], None, name)
 
 
+# 64 KV heads: workgroups of several 16-token tiles per wave, so tokens wait in the ring from tile to
+# tile.  Rank mixes from one token in 20 to all; sequences that end inside a later tile and group;
+# r_b up to 64 runs 8 waves (128 tokens a group), above 6 (96); r_b 128 moves 17 pieces of a row
+RING_CASES = [
+    ("ring-rb128", 128, (0, 4, 16), (0.5, 0.3, 0.2), [203, 420, 1, 170], (5, 790), "f16"),
+    ("ring-rb96-i8", 96, (0, 6, 16), (0.7, 0.2, 0.1), [610, 17, 160], (3, 785), "int8"),
+    ("ring-rb48-few", 48, (0, 8), (0.95, 0.05), [2060], (9, 2060), "f16"),
+    ("ring-rb32-i8", 32, (0, 2, 64), (0.4, 0.4, 0.2), [129, 514, 0, 640], (0, 1283), "int8"),
+    ("ring-rb16-all-ranked", 16, (2, 8), (0.5, 0.5), [500, 533], (7, 1033), "f16"),
+]
+
+
+@pytest.mark.parametrize("case", RING_CASES, ids=[c[0] for c in RING_CASES])
+def test_compress_ring_bit_exact(case):
+    """The prompt kernel with 2 to 4 tiles per wave: tokens with entries that wait
+    across tiles, the ring's wrap, the inputs loaded a tile ahead, and a basis
+    change while tokens of the last sequence wait."""
+    torch_gpu()
+    name, rb, levels, probs, lengths, (t0, t1), fmt = case
+    w = _Fixed(Workload(name=name, batch=len(lengths), n_layers=1, window=1, n_kv_heads=64, n_q_heads=64,
+                        head_dim=128, context=max(lengths), basis_rank=rb, levels=levels, probs=probs,
+                        q_dtype="bf16", seed=800 + len(name), coef_format=fmt), lengths)
+    host = generate(w, threads=4)
+    rng = np.random.default_rng(13 + len(name))
+    gate = rng.uniform(0.0, 1.0, size=(2, host.n_kv_heads, t1 - t0)).astype(np.float32)
+    _run_case(host, device_cache(host), [0], t0, t1, [_inputs(host, 0, t0, t1, "normal", rng)], [gate], None, name)
+
+
 def test_compress_zero_residual_and_ties():
     """Signed-permutation bases: inputs on the basis channels leave r = 0 exactly
     (scale 0, codes 0, channels 0..rho-1 by the tie rule); inputs with repeated
