@@ -336,6 +336,75 @@ def test_compress_zero_residual_and_ties():
     assert list(ref.res_idx[1, 0, 0, e0:e0 + rho]) == list(range(rho)), "zero residual must keep channels 0.."
 
 
+@pytest.mark.parametrize("rb,fmt", [(48, "f16"), (96, "f16"), (32, "int8")])
+def test_compress_tiles_odd_tokens(rb, fmt):
+    """Tokens the oracle has no answer for, with ordinary ones between them: a call
+    over the whole range (the prompt kernel) against calls of 4 tokens (one wave
+    per token), byte for byte.  Offsets that disagree with the rank, are odd, or
+    end past the entries' arrays (scale written, entries left alone); a level
+    beyond the table (rank 0); inputs of the type's largest values, infinite and
+    not a number, whose residuals are infinite or not a number in part or whole."""
+    torch = torch_gpu()
+    lengths = [150, 51]
+    w = _Fixed(Workload(name=f"odd{rb}", batch=2, n_layers=1, window=1, n_kv_heads=2, n_q_heads=2, head_dim=128,
+                        context=150, basis_rank=rb, levels=(0, 4, 16), probs=(0.3, 0.4, 0.3), q_dtype="f16",
+                        seed=31 + rb, coef_format=fmt), lengths)
+    host = generate(w, threads=4)
+    host.basis = host.basis.copy()
+    host.basis[1, 0, 1] *= np.float16(32.0)                  # sums past the fp16 range
+    T, Hk = host.total_tokens, host.n_kv_heads
+    rng = np.random.default_rng(rb)
+    xs = [rng.standard_normal((T, Hk, 128)).astype(np.float16) for _ in range(2)]
+    with np.errstate(over="ignore"):
+        for x in xs:
+            for k, t in enumerate(range(2, T, 5)):
+                kind, c = k % 6, rng.choice(128, size=3, replace=False)
+                if kind == 0:
+                    x[t, :, c] = np.float16(np.inf)
+                elif kind == 1:
+                    x[t, :, c] = np.array([[np.nan], [1.0], [-np.inf]], np.float16)
+                elif kind == 2:
+                    x[t] *= np.float16(60000.0)              # the largest values, infinities among them
+                elif kind == 3:
+                    x[t] = rng.choice([-65504.0, 65504.0], size=x[t].shape)
+                elif kind == 4:
+                    x[t] = 0
+                else:
+                    x[t] = np.float16(6e-8)                  # the smallest value
+    off = host.res_off.copy()
+    codes = host.rank_code.copy()
+    untouched = []
+    for h in range(Hk):
+        ranked = np.nonzero(codes[0, h, :T - 8])[0]
+        a, b, c = ranked[[3, 17, 40]]      # a longer, a shorter, one at odd offsets: their neighbours disagree too
+        untouched += [(h, off[0, h, a], off[0, h, a + 2]), (h, off[0, h, b], off[0, h, b + 2]),
+                      (h, off[0, h, c - 1], off[0, h, c + 2])]
+        off[0, h, a + 1] += 2
+        off[0, h, b + 1] -= 2
+        off[0, h, c:c + 2] += 1
+        codes[0, h, [33, 97]] = (3, 255)
+    codes[0, 0, T - 1] = codes[0, 1, T - 1] = 1
+    off[0, 0, T - 1:] = (host.res_stride - 2, host.res_stride + 2)
+    off[0, 1, T - 1:] = (2 ** 32 - 8, 2 ** 32 - 4)
+    host.res_off, host.rank_code = off, codes
+    dev = [torch.from_numpy(x).cuda() for x in xs]
+    whole, steps = device_cache(host), device_cache(host)
+    announce(f"compress odd tokens r_b {rb} {fmt}")
+    whole.compress(0, *dev, 0, T)
+    for t in range(0, T, 4):
+        e = min(t + 4, T)
+        steps.compress(0, dev[0][t:e].contiguous(), dev[1][t:e].contiguous(), t, e)
+    torch.cuda.synchronize()
+    a, b = _host_arrays(whole), _host_arrays(steps)
+    for name in (WRITTEN_I8 if fmt == "int8" else WRITTEN):
+        same = a[name].view(np.uint8).reshape(-1) == b[name].view(np.uint8).reshape(-1)
+        assert same.all(), f"{name}: {np.count_nonzero(~same)} bytes differ, first at {np.argmin(same)}"
+    assert not np.isfinite(a["res_scale"].astype(np.float32)).all(), "no residual left the finite range"
+    idx = a["res_idx"].reshape(2, Hk, -1)
+    for h, e0, e1 in untouched:
+        assert np.array_equal(idx[:, h, e0:e1], host.res_idx[0, :, h, e0:e1]), f"entries {e0}..{e1} of head {h}"
+
+
 def test_compress_full_size_sampled():
     """The 64K-token shape (r_b 48, 8 KV heads): a whole-layer compress in one
     launch, sampled tokens against the oracle bit for bit, then the validator."""
