@@ -123,13 +123,17 @@ def test_materialize_and_unfused(case):
 
 # r_b and lengths per workgroup size: launches of few blocks take one block per wave (64 tokens a
 # workgroup), 8 heads of 10K tokens two (128); r_b 32 and 48 keep the basis in registers and in LDS,
-# and rank 32 has entries past the 16 loaded ahead
+# and rank 32 has entries past the 16 loaded ahead.  64 heads of 5K to 6K tokens give a wave 9 or 10
+# blocks, whose offsets, coefficients and entries come from two and one blocks earlier; their
+# sequences end in a workgroup's first, middle and last blocks
 EDGES = [
     ("rb32-one-token-block", 32, 2, (0, 8, 32), (0.3, 0.4, 0.3), [1, 15, 16, 17, 32]),
     ("rb48-one-workgroup", 48, 2, (0, 8, 32), (0.3, 0.4, 0.3), [64, 63, 1, 128]),
     ("rb64-second-block", 64, 8, (0, 4), (0.5, 0.5), [8191, 2050]),
     ("rb96-straddled-workgroups", 96, 8, (4, 16), (0.5, 0.5), [127, 10001, 120]),
     ("rb112-tail", 112, 2, (0, 16), (0.9, 0.1), [321]),
+    ("rb32-long-waves", 32, 64, (0, 4, 16), (0.6, 0.2, 0.2), [5, 4095, 1, 1000, 17]),
+    ("rb48-long-waves", 48, 64, (0, 8, 32), (0.3, 0.4, 0.3), [2500, 30, 700, 1900]),
 ]
 
 
