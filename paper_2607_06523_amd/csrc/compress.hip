@@ -3,8 +3,8 @@
 // residual entries and gate-folded scales, written in place into the cache.
 //
 // Two kernels with the same results bit for bit:
-//  * compress_kernel, for a few tokens: one wave takes one token at a time
-//    (the arithmetic of one token is in compress_dev.h).
+//  * compress_kernel, for a few tokens: one wave takes one token (its arithmetic
+//    is in compress_dev.h).
 //  * compress_tile_kernel, for prompts: one wave takes 16 tokens, the
 //    projection and the basis term as products on v_mfma_f32_16x16x4_f32.
 //    That instruction adds its four products to the accumulator one after
@@ -25,8 +25,7 @@ namespace {
 
 using namespace cdev;
 
-constexpr int kCW = 4;                   // waves per workgroup
-constexpr int kCT = 64;                  // tokens per workgroup
+constexpr int kCW = 4;                   // waves of the one-wave-per-token kernel's workgroup
 struct Smem {
   uint16_t bas[kMaxRB * kBRow];          // basis rows of (sequence, window, head, Z)
   float xs[kCW][D];                      // the wave's input vector
@@ -72,21 +71,19 @@ __device__ __forceinline__ Slab make_slab(const CompressArgs& a, int h, int z) {
   return sl;
 }
 
-// grid (ceil(n / 64), Hkv, 2)
+// grid (ceil(n / 4), Hkv, 2): a wave takes one token
 __global__ __launch_bounds__(kCW * 64) void compress_kernel(const CompressArgs a) {
   __shared__ __align__(16) Smem sm;
   const int h = blockIdx.y, z = blockIdx.z;
   const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const Slab sl = make_slab(a, h, z);
-  const int64_t c0 = a.t0 + (int64_t)blockIdx.x * kCT;
-  const int64_t c1 = min(c0 + (int64_t)kCT, a.t0 + a.n);
+  const int64_t c0 = a.t0 + (int64_t)blockIdx.x * kCW, end = min(c0 + kCW, a.t0 + a.n), t = c0 + wv;
   const int rb = a.rb;
-  for (int b = sequence_of(a.cu, a.batch, c0); b < a.batch && (int64_t)a.cu[b] < c1; ++b) {
-    const int64_t s0 = max(c0, (int64_t)a.cu[b]), s1 = min(c1, (int64_t)a.cu[b + 1]);
+  TokenIn in = {};
+  if (t < end) in = load_token(a, sl, lane, h, z, t);     // in flight while the basis loads
+  for (int b = sequence_of(a.cu, a.batch, c0); b < a.batch && (int64_t)a.cu[b] < end; ++b) {
+    const int64_t s0 = max(c0, (int64_t)a.cu[b]), s1 = min(end, (int64_t)a.cu[b + 1]);
     if (s1 <= s0) continue;              // empty sequence (uniform over the workgroup)
-    int64_t t = s0 + wv;
-    TokenIn cur = {};
-    if (t < s1) cur = load_token(a, sl, lane, h, z, t);   // in flight while the basis loads
     __syncthreads();                     // every wave is done with the previous basis
     const uint16_t* src = a.basis + (int64_t)b * a.basis_b_stride + (int64_t)(h * 2 + z) * rb * D;
     for (int e = threadIdx.x; e < rb * (D / 8); e += kCW * 64) {
@@ -95,12 +92,8 @@ __global__ __launch_bounds__(kCW * 64) void compress_kernel(const CompressArgs a
           *reinterpret_cast<const uint4*>(src + (int64_t)i * D + 8 * q);
     }
     __syncthreads();
-    for (; t < s1; t += kCW) {
-      TokenIn nxt = cur;
-      if (t + kCW < s1) nxt = load_token(a, sl, lane, h, z, t + kCW);
-      compress_token(a, sl, CWave{sm.bas, sm.xs[wv], sm.as[wv], sm.ech[wv], sm.ecode[wv]}, lane, z, t, cur);
-      cur = nxt;
-    }
+    if (t >= s0 && t < s1)
+      compress_token(a, sl, CWave{sm.bas, sm.xs[wv], sm.as[wv], sm.ech[wv], sm.ecode[wv]}, lane, z, t, in);
   }
 }
 
@@ -712,18 +705,21 @@ void launch_tile(const CompressArgs& a, hipStream_t s) {
   else hipLaunchKernelGGL((compress_tile_kernel<RB, false>), grid, dim3(WT * 4), 0, s, a, (int)per);
 }
 
-// Ranges of up to four tokens (one for each wave of a workgroup) keep the
-// one-wave-per-token kernel: 8.3 us at r_b 48 and 14 at r_b 128, against 11 and
-// 19 for a tile, whose products' latency is the same for 1 token and 16.  From
-// five tokens on its waves take a second token each: 13.8 and 24.5 us.
-constexpr int64_t kFewTokens = 4;
+// Short ranges keep the one-wave-per-token kernel, whose time holds as long as
+// its workgroups run at once, 8.4 us at r_b 48 and 13.8 at r_b 128.  A tile's
+// products take the same time for 1 token and 16: 12 and 21 us from 5 tokens on
+// in fp16, 20 to 22 and 41 to 43 us in int8, whose basis term runs on the vector
+// units.  The line is where tiles overtook a workgroup of four waves that took
+// the range's tokens in turn: 13.9 and 24 us for 5 fp16 tokens; in int8 14.6 and
+// 25 us for 5, 20 and 37 for 12, 26 and 47 for 16.
+constexpr int64_t kFewTokens = 4, kFewTokensI8 = 15;
 
 }  // namespace
 
 hipError_t launch_compress(const CompressArgs& a, hipStream_t s) {
   if (a.n <= 0) return hipSuccess;
-  if (a.n <= kFewTokens) {
-    const unsigned nb = (unsigned)((a.n + kCT - 1) / kCT);
+  if (a.n <= (a.c8 ? kFewTokensI8 : kFewTokens)) {
+    const unsigned nb = (unsigned)((a.n + kCW - 1) / kCW);
     hipLaunchKernelGGL(compress_kernel, dim3(nb, a.n_kv_heads, 2), dim3(kCW * 64), 0, s, a);
     return hipGetLastError();
   }

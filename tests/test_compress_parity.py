@@ -271,6 +271,24 @@ def test_compress_tiles_bit_exact(case):
     _run_case(host, device_cache(host), [1], t0, t1, [_inputs(host, 1, t0, t1, "normal", rng)], [gate], None, name)
 
 
+@pytest.mark.parametrize("rb,fmt,t0,t1", [(48, "f16", 6, 10), (128, "f16", 2, 5), (96, "int8", 7, 9),
+                                          (16, "int8", 8, 12), (48, "int8", 5, 10), (128, "int8", 2, 17),
+                                          (32, "int8", 1, 17)])
+def test_compress_few_tokens(rb, fmt, t0, t1):
+    """Short ranges of up to four sequences: one wave per token for up to 4 tokens
+    (int8: 15), workgroups of four; the last case is the first on tiles."""
+    torch_gpu()
+    lengths = [3, 5, 1, 0, 9]
+    w = _Fixed(Workload(name=f"few{rb}", batch=len(lengths), n_layers=2, window=2, n_kv_heads=2, n_q_heads=4,
+                        head_dim=128, context=max(lengths), basis_rank=rb, levels=(0, 4, 16), probs=(0.2, 0.4, 0.4),
+                        q_dtype="bf16", seed=60 + rb, coef_format=fmt), lengths)
+    host = generate(w, threads=4)
+    rng = np.random.default_rng(rb)
+    gate = rng.uniform(0.0, 1.0, size=(2, host.n_kv_heads, t1 - t0)).astype(np.float32)
+    _run_case(host, device_cache(host), [1], t0, t1, [_inputs(host, 1, t0, t1, "normal", rng)], [gate], None,
+              f"few rb{rb} {fmt}")
+
+
 # 64 KV heads: workgroups of several 16-token tiles per wave, so tokens wait in the ring from tile to
 # tile.  Rank mixes from one token in 20 to all; sequences that end inside a later tile and group;
 # r_b up to 64 runs 8 waves (128 tokens a group), above 6 (96); r_b 128 moves 17 pieces of a row
