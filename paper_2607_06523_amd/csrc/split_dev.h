@@ -36,11 +36,11 @@
 //    written by the token lanes; key entries add into an LDS score buffer,
 //    value entries into an LDS d-vector per head (ds_add_f32).
 //  * the query's projection into basis space and the epilogue's B^V product run
-//    on v_mfma_f32_16x16x4_f32, so they keep float32 multiply-adds.  A chunk is
-//    few tiles per wave and LDS holds one workgroup per CU for large groups, so
-//    these ends are latency: at G 16, r_b 96, 16K tokens of 4 KV heads a decode
-//    call takes 32 us, and took 57 with one thread per row or output and the
-//    B^V rows requested only at the end.
+//    on v_mfma_f32_16x16x4_f32 for groups of 4 and more, so they keep float32
+//    multiply-adds.  A chunk is few tiles per wave and LDS holds one workgroup
+//    per CU for large groups, so these ends are latency: at G 16, r_b 96, 16K
+//    tokens of 4 KV heads a decode call takes 32 us, and took 57 with one thread
+//    per row or output and the B^V rows requested only at the end.
 //  * epilogue: the 4 waves merge (m, l, a~, r) in LDS, project a~ through B^V
 //    and write one partial (o, m, l) per query head; a merge kernel combines
 //    the splits (and computes Eq. 3's error for probed heads).
@@ -106,6 +106,13 @@ constexpr int kFxTopG = 42;
 
 template <int RB, int G>
 constexpr bool kFixedResid = G <= 8 || RB <= 96;
+
+// Groups whose basis products run on the matrix cores.  A 16-row tile takes the
+// same time for 1 head and 16: at 16K tokens of 8 KV heads, r_b 80, a call takes
+// 22.3 us at G 1 and 23.4 at G 2 with them, 19.6 and 22.0 with one thread per
+// row or output; at G 4 34.5 and 41.6.
+template <int G>
+constexpr bool kMatrixEnds = G > 2;
 
 template <int RB, int G, bool RESID>
 struct alignas(16) WaveSmem {
@@ -622,7 +629,8 @@ __device__ __forceinline__ void split_body(const SplitArgs& a, int w, int slot, 
   // tile's coefficient fragments; last its residual entries, whose addresses
   // need the offsets.  Every load is unconditional (a wave with no tile reads
   // the chunk's last one and never uses it).
-  constexpr int NIT = (NS + NW - 1) / NW;                    // q~ row tiles per wave
+  // q~ row tiles per wave, or quarter rows per thread
+  constexpr int NIT = kMatrixEnds<G> ? (NS + NW - 1) / NW : (RB * 4 + kThreads - 1) / kThreads;
   constexpr int QPT = (G * D + kThreads - 1) / kThreads;     // query elements per thread
   constexpr int BVQ = IDENT ? 1 : RB * D / 8 / kThreads;     // 16-byte B^V chunks per thread
   const int j0 = min(wv, x.ntile - 1);
@@ -643,11 +651,12 @@ __device__ __forceinline__ void split_body(const SplitArgs& a, int w, int slot, 
     const int i = min(tid + n * kThreads, G * D - 1);
     qraw[n] = a.q[((int64_t)b * a.n_q_heads + kvh * G + i / D) * D + i % D];
   }
-  if constexpr (!IDENT) {               // lane (col, grp): row col of the tile, channels 32 grp .. + 31
+  if constexpr (!IDENT) {               // tile: lane (col, grp) has row col, channels 32 grp .. + 31
 #pragma unroll
     for (int n = 0; n < NIT; ++n) {
-      const int tile = min(wv + n * NW, NS - 1);
-      const uint4* row = reinterpret_cast<const uint4*>(bk_rows + (16 * tile + col) * D + 32 * grp);
+      const int it = min(tid + n * kThreads, RB * 4 - 1), tile = min(wv + n * NW, NS - 1);
+      const int k = kMatrixEnds<G> ? 16 * tile + col : it >> 2, quarter = kMatrixEnds<G> ? grp : it & 3;
+      const uint4* row = reinterpret_cast<const uint4*>(bk_rows + k * D + 32 * quarter);
 #pragma unroll
       for (int i = 0; i < 4; ++i) rv[n][i] = row[i];
     }
@@ -658,7 +667,7 @@ __device__ __forceinline__ void split_body(const SplitArgs& a, int w, int slot, 
   __builtin_amdgcn_sched_barrier(0);
   if constexpr (RESID) load_entries<TT>(ec, x, mc, lane);
   u4v bvr[BVQ];                         // B^V rows, for the epilogue's projection
-  if constexpr (!IDENT) {
+  if constexpr (!IDENT && kMatrixEnds<G>) {
 #pragma unroll
     for (int n = 0; n < BVQ; ++n) bvr[n] = reinterpret_cast<const u4v*>(bv_rows)[tid + n * kThreads];
   }
@@ -670,7 +679,37 @@ __device__ __forceinline__ void split_body(const SplitArgs& a, int w, int slot, 
       sm.qs[i % D][i / D] = (a.q_bf16 ? bf16_bits_to_float(qraw[n]) : half_bits_to_float(qraw[n])) * a.qscale;
   }
   __syncthreads();
-  if constexpr (!IDENT) {
+  if constexpr (!IDENT && !kMatrixEnds<G>) {
+    // q~: four threads per basis row, 32 channels each
+#pragma unroll
+    for (int n = 0; n < NIT; ++n) {
+      const int it = tid + n * kThreads;
+      if (it >= RB * 4) continue;
+      const int k = it >> 2, qq = it & 3;
+      float acc[G];
+#pragma unroll
+      for (int g = 0; g < G; ++g) acc[g] = 0.f;
+#pragma unroll
+      for (int e = 0; e < 32; ++e) {
+        const uint32_t dw = dword_at(rv[n][e >> 3], (e >> 1) & 3);
+        const float xv = half_bits_to_float((uint16_t)((e & 1) ? (dw >> 16) : (dw & 0xFFFF)));
+#pragma unroll
+        for (int g = 0; g < G; ++g) acc[g] += xv * sm.qs[qq * 32 + e][g];
+      }
+#pragma unroll
+      for (int g = 0; g < G; ++g) {
+        acc[g] += __shfl_xor(acc[g], 1);
+        acc[g] += __shfl_xor(acc[g], 2);
+      }
+      if (qq == 0) {
+#pragma unroll
+        for (int g = 0; g < G; ++g) {
+          sm.qt[g][k] = acc[g];
+          atomicMax(&sm.qmax[g], __float_as_int(fabsf(acc[g])));
+        }
+      }
+    }
+  } else if constexpr (!IDENT) {
     // q~ tiles on v_mfma_f32_16x16x4_f32 (16 basis rows x 16 heads, float32
     // multiply-adds): lane group grp's k-step u is channel 32 grp + u
 #pragma unroll
@@ -745,7 +784,7 @@ __device__ __forceinline__ void split_body(const SplitArgs& a, int w, int slot, 
   // the last of them at once), so the loop's own waits count only the loop's
   // loads and stay exact.
   __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);
-  if constexpr (!IDENT) {               // read after the epilogue's barriers
+  if constexpr (!IDENT && kMatrixEnds<G>) {   // read after the epilogue's barriers
 #pragma unroll
     for (int n = 0; n < BVQ; ++n) reinterpret_cast<u4v*>(&sm.bvs[0][0])[tid + n * kThreads] = bvr[n];
   }
@@ -772,6 +811,10 @@ __device__ __forceinline__ void split_body(const SplitArgs& a, int w, int slot, 
       const int g = 4 * grp + i;
       if (g < G) sm.ep_a[wv][g][16 * cb + col] = st.acc[cb][i];
     }
+  if constexpr (!IDENT && !kMatrixEnds<G>) {   // requested while the waves merge
+#pragma unroll
+    for (int n = 0; n < BVQ; ++n) bvr[n] = reinterpret_cast<const u4v*>(bv_rows)[tid + n * kThreads];
+  }
   __syncthreads();
   if (tid < G) {
     const int g = tid;
@@ -786,6 +829,10 @@ __device__ __forceinline__ void split_body(const SplitArgs& a, int w, int slot, 
     sm.mstar[g] = mx;
     sm.lstar[g] = l;
   }
+  if constexpr (!IDENT && !kMatrixEnds<G>) {
+#pragma unroll
+    for (int n = 0; n < BVQ; ++n) reinterpret_cast<u4v*>(&sm.bvs[0][0])[tid + n * kThreads] = bvr[n];
+  }
   __syncthreads();
   for (int i = tid; i < G * RB; i += kThreads) {
     const int g = i / RB, k = i % RB;
@@ -795,11 +842,27 @@ __device__ __forceinline__ void split_body(const SplitArgs& a, int w, int slot, 
   }
   __syncthreads();
   float* const part_ws = a.part;
-  if constexpr (IDENT) {
+  if constexpr (IDENT || !kMatrixEnds<G>) {
     const int c_out = tid % D, par = tid / D;
     for (int g = par; g < G; g += kThreads / D) {
+      float o;
+      if constexpr (IDENT) {
+        o = sm.acomb[g][c_out];
+      } else {
+        o = 0.f;
+#pragma unroll 16
+        for (int k = 0; k < RB; ++k) o += sm.acomb[g][k] * half_bits_to_float(sm.bvs[k][c_out]);
+      }
+      if constexpr (RESID) {
+        for (int v = 0; v < NW; ++v) {
+          if constexpr (kFixedResid<RB, G>)
+            o += sm.sw[v][g] * (fixed_to_float(sm.w[v].racc[g][c_out]) * ldexpf(1.0f, sm.w[v].ex - kFxTopG));
+          else
+            o += sm.sw[v][g] * sm.w[v].racc[g][c_out];
+        }
+      }
       float* dst = part_ws + (((int64_t)w * a.n_slots + slot) * G + g) * kPartStride;
-      dst[c_out] = sm.acomb[g][c_out];
+      dst[c_out] = o;
       if (c_out == 0) {
         dst[D] = sm.mstar[g];
         dst[D + 1] = sm.lstar[g];

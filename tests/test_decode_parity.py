@@ -36,6 +36,10 @@ SMALL = [
     ("rb80-g16-short-tiles", 80, 16, (0, 8), (0.5, 0.5), [333], 64, "f16"),
     ("rb96-g1-no-residual", 96, 1, (0,), (1.0,), [500, 37], 128, "bf16"),
     ("rb112-g2", 112, 2, (0, 2, 6), (0.3, 0.3, 0.4), [777], 256, "bf16"),
+    # general kernel at its small groups with entries (ranks above 16 below r_b 80)
+    ("rb16-g2-rank32", 16, 2, (0, 32), (0.4, 0.6), [300, 65, 0, 1], 64, "bf16"),
+    ("rb48-g1-rank64", 48, 1, (0, 8, 64), (0.5, 0.3, 0.2), [900, 17], 0, "f16"),
+    ("rb128-g1-entries", 128, 1, (0, 4, 16), (0.4, 0.4, 0.2), [333, 1500], 192, "bf16"),
     ("rb128-g4-full-rank-residual", 128, 4, (0, 128), (0.5, 0.5), [257, 70], 128, "bf16"),
     ("rb32-g16-many-entries", 32, 16, (32, 64), (0.5, 0.5), [200, 4097], 0, "bf16"),
     # token-lane kernel: ~900 entries per 64-token tile (past the preloaded batches)
