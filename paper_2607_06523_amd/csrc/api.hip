@@ -75,7 +75,8 @@ int64_t count_work(const dwkv_dims* d, int split, int trim = 0);
 int plan_split(const dwkv_dims* d) {
   if (d->split_tokens > 0) return d->split_tokens;
   const int64_t work = d->total_tokens * d->n_kv_heads;
-  // one workgroup per CU for the token-lane kernel (8 waves), two for the general one (4 waves)
+  // one workgroup per CU for the token-lane kernel (8 waves), two for the general one (4 waves),
+  // also where its LDS lets a CU hold only one, as G 16 at r_b 96: those run in two rounds
   const int64_t target = uses_token_lane(d) ? kTargetWorkgroups / 2 : kTargetWorkgroups;
   int64_t c = (work + target - 1) / target;
   c = (c + kSplitQuantum - 1) / kSplitQuantum * kSplitQuantum;

@@ -162,8 +162,8 @@ __global__ __launch_bounds__(kRT) void route_offsets_kernel(const RouteArgs a) {
 //
 // Ranges of up to kBudgetOne tokens run in one workgroup per (window, head),
 // the scores held in registers.  Longer ones spread over the chip in six
-// launches (clear 3 us, three digits 15, 12 and 6, counts 6, write 13): 64
-// pairs of 64K tokens take 56 us (their 88 MB of features and results alone 18
+// launches (clear 3 us, three digits 16, 12 and 6, counts 7, write 11): 64
+// pairs of 64K tokens take 52 to 55 us (their 88 MB of features and results alone 18
 // at the copy rate) and are bound by the launches and by the histograms'
 // atomics.  One workgroup per pair with eight passes over 64-bit keys in memory
 // took 540 us.  For 1024 and 16384 tokens the single launch takes 12 and 18 us,

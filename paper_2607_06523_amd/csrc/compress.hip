@@ -10,12 +10,14 @@
 //    That instruction adds its four products to the accumulator one after
 //    the other, each rounded as a fused multiply-add would, so a chain of them
 //    is the left-to-right sum the results are defined by (fp16 products are
-//    exact in float32).  Bound by its instructions, the products' 32 cycles each
-//    beside the selection of the entries: a layer of 32K tokens and 8 KV heads
-//    (r_b 48) takes 130 us with one token in four holding entries and 215 us
-//    with nearly all of them, where compress_kernel takes 680 us (19 TFLOP/s of
-//    the two products against 100).  Forming the basis term and the entries
-//    tile by tile, for tokens without entries too, took 190 to 220 us.
+//    exact in float32).  Bound by its instructions, the products and after them
+//    the selection of the entries, and by their chains: with one token in three
+//    holding entries the matrix cores are busy 25 % and vector instructions issue
+//    38 % of a SIMD's cycles, and a wave waits on a dependency for 37 % of its
+//    own.  A layer of 32K tokens and 8 KV heads (r_b 48) takes 129, 190 and 359
+//    us with one token in twenty, one in four and every token holding entries
+//    (100, 68 and 36 TFLOP/s of the two products, tokens without entries counted
+//    in full); one token per wave, four waves to 64 tokens, took 629, 702 and 875.
 #include <algorithm>
 
 #include "compress_dev.h"
@@ -698,7 +700,10 @@ void launch_tile(const CompressArgs& a, hipStream_t s) {
   const int64_t n16 = a.n + (a.t0 & 15), ng = (n16 + WT - 1) / WT;
   // groups per workgroup (each loads the basis once and ends with a partly
   // filled batch of waiting tokens): as many as leave two rounds of the one
-  // workgroup a compute unit holds
+  // workgroup a compute unit holds, up to 64.  128K tokens of 8 KV heads (r_b 48)
+  // take 774 us, with one round 763 and with four 803; at r_b 96 1739, 2105 and
+  // 1728.  512K tokens take 2.54 ms with up to 64 groups, 2.67 with up to 16 and
+  // 2.51 with no limit.
   const int64_t per = std::max<int64_t>(1, std::min<int64_t>(64, ng * a.n_kv_heads * 2 / 512));
   const dim3 grid((unsigned)((ng + per - 1) / per), a.n_kv_heads, 2);
   if (a.c8) hipLaunchKernelGGL((compress_tile_kernel<RB, true>), grid, dim3(WT * 4), 0, s, a, (int)per);

@@ -8,10 +8,13 @@
 //  1. split-K sketch partials on v_mfma_f64_16x16x4_f64 (fp16 products are
 //     exact in float64), one workgroup per (4096-row chunk, head, Z),
 //     each of its 4 waves owning 32 channels and every row of Omega.  Bound by
-//     the float64 matrix rate: the 51.5 GFLOP of a 4 x 64K window (r_b 48, 8
-//     heads) take 0.87 ms, 59 TFLOP/s of the published 78.6; one thread per
-//     channel on float64 FMAs, converting Omega's row in every thread, took
-//     6.1 ms.
+//     the float64 matrix rate where the workgroups fill the chip: the 51.5 GFLOP
+//     of a 4 x 64K window (r_b 48, 8 heads; 1024 workgroups) take 0.91 ms, 57
+//     TFLOP/s of the published 78.6, the matrix cores busy 77 % of the cycles; one
+//     thread per channel on float64 FMAs, converting Omega's row in every thread,
+//     took 6.1 ms.  Below a workgroup for each of the 256 compute units (4 x 16K
+//     tokens of 8 heads) the call takes 265 to 290 us from 4096 rows on: one
+//     chunk's rows in turn, and the Gram-Schmidt.
 //  2. the chunk partials summed in chunk order, one thread per element (50 MB
 //     read once in 10 us; inside the orthonormalization one compute unit would
 //     pull each head's share).
@@ -82,11 +85,12 @@ __device__ __forceinline__ void sk_mma(d4 (&acc)[NS][2], const SkRows<NS>& f) {
   }
 }
 
-// grid (chunks, Hkv, 2); a chunk runs over the layers that its rows lie in.  Of the MFMA operands, lane (r, kk) =
-// (lane % 16, lane / 16) holds row r (A) or column r (B) at depth kk, and the
-// result's rows 4 i + kk of column r.  Operand rows and columns are dealt so
-// that a lane's loads are contiguous: A row r of tile s is Omega entry
-// NS r + s, B column r of tile c is channel 2 r + c of the wave's 32.
+// grid (chunks, Hkv, 2); a chunk runs over the layers that its rows lie in.  Of
+// the MFMA operands, lane (r, kk) = (lane % 16, lane / 16) holds row r (A) or
+// column r (B) at depth kk, and the result's rows 4 i + kk of column r.  Operand
+// rows and columns are dealt so that a lane's loads are contiguous: A row r of
+// tile s is Omega entry NS r + s, B column r of tile c is channel 2 r + c of the
+// wave's 32.
 template <int RB>
 __global__ __launch_bounds__(64 * kSkWaves) void sketch_partial_kernel(const SketchArgs a) {
   constexpr int NS = RB / 16;

@@ -66,8 +66,9 @@ def test_sketch_small(rb, n_tok, kind):
 @pytest.mark.parametrize("rb,n_tok", [(64, 1), (48, 31), (80, 33), (112, 129), (96, 257), (128, 4129)])
 def test_sketch_chunk_edges(rb, n_tok):
     """Prefills of one row, around a 32-row load group, with chunks of 4096 rows
-    that hold several layers or parts of them, and with odd and even r_b / 16 (the sketch operand's two load forms); the bar is
-    the fp16 rounding of float64 results, one step."""
+    that hold several layers or parts of them, and with odd and even r_b / 16 (the
+    sketch operand's two load forms); the bar is the fp16 rounding of float64
+    results, one step."""
     torch = torch_gpu()
     w = Workload(name=f"ske{rb}", batch=1, n_layers=3, window=3, n_kv_heads=2, n_q_heads=4, head_dim=128,
                  context=64, basis_rank=rb, levels=(0, 8), probs=(0.5, 0.5), q_dtype="bf16", seed=rb)
